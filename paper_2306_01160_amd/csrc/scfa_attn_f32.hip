@@ -54,7 +54,7 @@ template <int D, int KS, bool INDIRECT>
 __global__ __launch_bounds__(F32_QW * KS * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) void attn_fwd_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const uint32_t* __restrict__ q_key, const uint32_t* __restrict__ k_key,
-    const int32_t* __restrict__ work, int n_work, int S, int T, float tau, int strict, float* __restrict__ o,
+    const int32_t* __restrict__ work, int n_work, int first, int S, int T, float tau, int strict, float* __restrict__ o,
     float* __restrict__ lse, const int32_t* __restrict__ n_keep_q)
 {
     using L = F32Tiles<D, KS>;
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(F32_QW * KS * 64) __attribute__((amdgpu_waves_per_e
     uint32_t* keys_s = reinterpret_cast<uint32_t*>(f32_smem + L::KEY_OFF);
 
     const int s = blockIdx.x % S;
-    const int w = blockIdx.x / S;
+    const int w = first + blockIdx.x / S;
     const size_t seg = (size_t)s * T;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     if (n_keep_q) {   // QK-dropping: a share of the segment's dropped rows (zeros, LSE = -inf)
@@ -260,10 +260,12 @@ static int launch_f32_t(const float* q, const float* k, const float* v, const ui
     static std::atomic<unsigned long long> lds_allowed{0};
     const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_fwd_f32_kernel<D, KS, INDIRECT>), L::SMEM, lds_allowed);
     if (rc != SCFA_OK) return rc;
-    hipLaunchKernelGGL((attn_fwd_f32_kernel<D, KS, INDIRECT>), dim3((unsigned)((size_t)S * n_work)), dim3(L::THREADS), L::SMEM, st,
-                       q, k, v, q_key, k_key, work, n_work, S, T, tau, strict, o, lse, n_keep_q);
-    SCFA_HIP_TRY(hipGetLastError());
-    return SCFA_OK;
+    return launch_in_grids(S, n_work, L::THREADS, [&](int first, unsigned items) -> int {
+        hipLaunchKernelGGL((attn_fwd_f32_kernel<D, KS, INDIRECT>), dim3(S * items), dim3(L::THREADS), L::SMEM, st, q, k, v, q_key, k_key,
+                           work, n_work, first, S, T, tau, strict, o, lse, n_keep_q);
+        SCFA_HIP_TRY(hipGetLastError());
+        return SCFA_OK;
+    });
 }
 
 // indirect: q, k, v are the tensors in original order, fetched through the positions in the sort keys

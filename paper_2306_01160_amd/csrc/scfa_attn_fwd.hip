@@ -86,7 +86,7 @@ template <int D, int NW, int QB, bool OWN_Q, int KS>
 __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && KS == 1 ? 3 : 2))) void attn_fwd_f16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint32_t* __restrict__ q_key, const uint32_t* __restrict__ k_key,
-    const int32_t* __restrict__ work, int n_work, int S, int T, float tau, int strict,
+    const int32_t* __restrict__ work, int n_work, int first, int S, int T, float tau, int strict,
     uint16_t* __restrict__ o, float* __restrict__ lse, uint16_t* __restrict__ o_f16, const int32_t* __restrict__ n_keep_q,
     uint16_t* __restrict__ q_out)
 {
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     // items of every segment are dispatched first, and when S is a multiple of 8 a segment
     // stays on one XCD (its K/V stay in that XCD's L2).
     const int s = blockIdx.x % S;
-    const int w = blockIdx.x / S;
+    const int w = first + blockIdx.x / S;
     const int32_t* it = work + ((size_t)s * n_work + w) * WORK_STRIDE;
     const int q_begin = it[W_QBEGIN], q_count = it[W_QCOUNT];
     const int k_begin = it[W_KBEGIN], k_count = it[W_KCOUNT], k_nomask = it[W_KNOMASK];
@@ -513,12 +513,13 @@ static int launch_fwd_t(const void* q, const void* k, const void* v, const uint3
     constexpr size_t smem = (size_t)KS * FwdRing<D>::NBUF * FwdRing<D>::BUF_BYTES;
     static std::atomic<unsigned long long> lds_allowed{0};
     { const int rc_ = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_fwd_f16_kernel<D, 4, 1, OWN_Q, KS>), (int)smem, lds_allowed); if (rc_ != SCFA_OK) return rc_; }
-    dim3 grid((unsigned)((size_t)S * n_work));
-    hipLaunchKernelGGL((attn_fwd_f16_kernel<D, 4, 1, OWN_Q, KS>), grid, dim3(256 * KS), smem, st, (const uint16_t*)q,
-                       (const uint16_t*)k, (const uint16_t*)v, q_key, k_key, work, n_work, S, T, tau,
-                       strict, (uint16_t*)o, lse, (uint16_t*)o_f16, n_keep_q, (uint16_t*)q_out);
-    SCFA_HIP_TRY(hipGetLastError());
-    return SCFA_OK;
+    return launch_in_grids(S, n_work, 256 * KS, [&](int first, unsigned items) -> int {
+        hipLaunchKernelGGL((attn_fwd_f16_kernel<D, 4, 1, OWN_Q, KS>), dim3(S * items), dim3(256 * KS), smem, st, (const uint16_t*)q,
+                           (const uint16_t*)k, (const uint16_t*)v, q_key, k_key, work, n_work, first, S, T, tau,
+                           strict, (uint16_t*)o, lse, (uint16_t*)o_f16, n_keep_q, (uint16_t*)q_out);
+        SCFA_HIP_TRY(hipGetLastError());
+        return SCFA_OK;
+    });
 }
 
 // workgroups of the forward kernel one CU holds at once (registers, LDS ring)

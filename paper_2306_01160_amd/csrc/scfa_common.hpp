@@ -74,6 +74,21 @@ constexpr int BWD_TILE_M = 64;   // query rows per inner step of the dK/dV kerne
 constexpr int F32_TILE_M = 64;   // fp32 path: query rows per workgroup (2 waves x 32, times the key splits)
 constexpr int F32_TILE_N = 32;   // keys per tile of one wave
 
+// ---- grids beyond 2^32 threads ---------------------------------------------------------------
+// A launch whose threads do not fit 32 bits runs only part of its workgroups and reports no error.  The attention kernels take a
+// workgroup per work item and segment, item-major, and the items from `first` on: launch(first, items) is called for as many
+// items at a time as one grid takes (all of them but with tens of thousands of segments and hundreds of items each).
+template <typename F>
+int launch_in_grids(int S, long long items, int threads, F launch)
+{
+    const long long most = 0xffffffffLL / ((long long)S * threads);     // S <= 65535, threads <= 512: at least 128
+    for (long long first = 0; first < items; first += most) {
+        const int rc = launch((int)first, (unsigned)(items - first < most ? items - first : most));
+        if (rc != SCFA_OK) return rc;
+    }
+    return SCFA_OK;
+}
+
 // ---- kernel launchers (defined in the .hip files) ---------------------------
 int launch_sort_by_bucket(int n_problems, const int32_t* bucket0, const int32_t* bucket1, int S, int T, int nb,
                           int32_t* idx0, int32_t* sorted0, int32_t* off0, uint32_t* key0, int32_t* idx1,
