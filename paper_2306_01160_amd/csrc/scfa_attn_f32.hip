@@ -130,8 +130,8 @@ __global__ __launch_bounds__(F32_QW * KS * 64) __attribute__((amdgpu_waves_per_e
     qhi_wave = __builtin_amdgcn_readfirstlane(qhi_wave);
 
     f32x16 acc[D / 32];
-    const float cexp = tau * LOG2E;    // scores, their maximum and the exponents in base-2 units
-    float m, l;                        // l: this lane's half of the sum
+    const float cexp = tau * LOG2E;    // probabilities are 2^(cexp (s - m)) of the raw scores <q, k>
+    float m, l;                        // m: raw, so that the logsumexp has the bits of tau m; l: this lane's half of the sum
     // Once, and again without the values that are not finite where a result is not (0 * inf in the products of masked keys, see
     // above): their rows then get them added.
     for (bool again = false;; again = true) {
@@ -206,18 +206,18 @@ __global__ __launch_bounds__(F32_QW * KS * 64) __attribute__((amdgpu_waves_per_e
                 const uint32_t kv[4] = {kp.x, kp.y, kp.z, kp.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    sacc[4 * g + e] = kv[e] - qlo > qspan ? -INFINITY : sacc[4 * g + e] * cexp;   // bucket and causal test
+                    sacc[4 * g + e] = kv[e] - qlo > qspan ? -INFINITY : sacc[4 * g + e];          // bucket and causal test
                     mx = fmaxf(mx, sacc[4 * g + e]);
                 }
             }
             const float m_new = fmaxf(m, half_max(mx));
             const float m_use = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = fast_exp2(m - m_use);   // m = -inf until the first taken key -> 0
+            const float alpha = fast_exp2((m - m_use) * cexp);   // m = -inf until the first taken key -> 0
             m = m_new;
             float sum = 0.f;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                sacc[i] = fast_exp2(sacc[i] - m_use);
+                sacc[i] = fast_exp2((sacc[i] - m_use) * cexp);
                 sum += sacc[i];
             }
             l = l * alpha + sum;
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(F32_QW * KS * 64) __attribute__((amdgpu_waves_per_e
                 const float m2 = mine[0], l2 = mine[64];
                 const float m_new = fmaxf(m, m2);
                 const float m_use = m_new == -INFINITY ? 0.f : m_new;
-                const float a1 = fast_exp2(m - m_use), a2 = fast_exp2(m2 - m_use);
+                const float a1 = fast_exp2((m - m_use) * cexp), a2 = fast_exp2((m2 - m_use) * cexp);
                 m = m_new;
                 l = l * a1 + l2 * a2;
 #pragma unroll
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(F32_QW * KS * 64) __attribute__((amdgpu_waves_per_e
         for (int g = 0; g < 4; ++g)
             *reinterpret_cast<float4*>(dst + db * 32 + 8 * g) =
                 make_float4(acc[db][4 * g] * inv, acc[db][4 * g + 1] * inv, acc[db][4 * g + 2] * inv, acc[db][4 * g + 3] * inv);
-    if (h == 0) lse[seg + qpos] = ltot > 0.f ? (m + log2f(ltot)) * LN2 : -INFINITY;
+    if (h == 0) lse[seg + qpos] = ltot > 0.f ? fmaf(log2f(ltot), LN2, m * tau) : -INFINITY;
 }
 
 template <int D, int KS, bool INDIRECT>

@@ -1,4 +1,4 @@
-"""fp32 forward: values at masked positions stay out of the rows that do not attend them."""
+"""fp32 forward: values at masked positions stay out of the rows that do not attend them, and the logsumexp of large scores."""
 import numpy as np
 import pytest
 import torch
@@ -60,3 +60,25 @@ def test_a_value_that_is_not_finite_reaches_only_the_rows_that_attend_it(variant
         reached[..., col] |= same & (at >= pos + int(strict))
     assert reached.any() and not torch.isfinite(o2[reached]).any()
     assert torch.equal(o[~reached], o2[~reached])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_logsumexp_keeps_the_bits_of_the_maximum(d):
+    """Whole-number rows: scores and, at a scale of 1/8, their multiples are exact.  A row of one key has that score for its
+    logsumexp, to the bit; with more keys the addition rounds once (half a unit in the last place) and the sum's logarithm
+    carries the rounding of exp2, log2 and at most 200 additions, a few 2^-24 of a number of at most log 200."""
+    rng = np.random.default_rng(d)
+    T, tau = 200, 0.125
+    q, k = (rng.integers(-12, 13, (1, 2, T, d)).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((1, 2, T, d), dtype=np.float32)
+    gq, gk, gv = (torch.from_numpy(x).cuda() for x in (q, k, v))
+    own = torch.arange(T, dtype=torch.int32, device="cuda").expand(1, 2, T).contiguous()
+    _, lse, _ = pipeline.hash_forward(gq, gk, gv, own, own, T, tau, need_bwd=False)
+    assert np.array_equal(lse.cpu().numpy(), (np.einsum("bhtd,bhtd->bht", q, k) * tau).astype(np.float32))
+    one = torch.zeros_like(own)
+    _, lse, _ = pipeline.hash_forward(gq, gk, gv, one, one, 1, tau, need_bwd=False)
+    s = np.einsum("bhid,bhjd->bhij", q.astype(np.float64), k.astype(np.float64)) * tau
+    s = np.where(np.tril(np.ones((T, T), bool)), s, -np.inf)
+    m = s.max(-1)
+    want = m + np.log(np.exp(s - m[..., None]).sum(-1))
+    assert np.all(np.abs(lse.cpu().numpy() - want) <= 0.5 * np.spacing(np.abs(want).astype(np.float32)) + 2.0 ** -20)
