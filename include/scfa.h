@@ -386,7 +386,8 @@ int scfa_qkdrop_attn_bwd(const void *q_c, const void *k_c, const void *v_c,
  *                   scfa_forward_workspace reports (SCFA_FWD_ABSENT: not there):
  *                     SCFA_FWD_Q_KEY, _K_KEY    [S,T] sort keys (qkdrop: compacted index vectors)
  *                     SCFA_FWD_Q_OFF, _K_OFF    [S,nb+1] bucket offsets (qkdrop: [S] kept counts)
- *                     SCFA_FWD_Q_PERM, _K_PERM, _V_PERM   [S,T,d] fp16 permuted rows (not for SCFA_F32: rows are read in place)
+ *                     SCFA_FWD_Q_PERM, _K_PERM, _V_PERM   [S,T,d] fp16 permuted rows (not for SCFA_F32: rows are read in place;
+ *                                                Q_PERM not for SCFA_BF16 without need_bwd: the kernel fetches its own queries)
  *                     SCFA_FWD_WORK, _BWD_WORK  work lists; SCFA_FWD_COUNTERS [S,4] int64
  *                     SCFA_FWD_O_F16            [B,H,T,d] fp16 copy of O (SCFA_BF16 with need_bwd)
  * scfa_backward: `fwd_ws` is the workspace of a forward with need_bwd and the same variant, sizes, dtype, scale and flags,

@@ -162,7 +162,8 @@ static int forward_layout(int variant, int S, int T, int d, int nb, int dtype, b
     if (need_bwd) L.off[SCFA_FWD_BWD_WORK] = take(4 * (size_t)S * L.n_bwd * WORK_STRIDE);
     L.off[SCFA_FWD_COUNTERS] = take(8 * (size_t)S * 4);
     if (!f32) {
-        L.off[SCFA_FWD_Q_PERM] = take(2 * rows * d);
+        // a forward of its own reads the bf16 queries in place (see own_q in scfa_forward): nobody writes or reads a copy
+        if (need_bwd || dtype == SCFA_F16) L.off[SCFA_FWD_Q_PERM] = take(2 * rows * d);
         L.off[SCFA_FWD_K_PERM] = take(2 * rows * d);
         L.off[SCFA_FWD_V_PERM] = take(2 * rows * d);
     }

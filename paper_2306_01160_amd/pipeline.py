@@ -22,7 +22,8 @@ class Context:
     """What a forward pass leaves for the backward.  Besides the fields below, as views of the workspace (None where
     the pass has no such thing):
 
-    q_p, k_p, v_p            [S,T,d] permuted rows in the compute format (fp32: rows are read in place)
+    q_p, k_p, v_p            [S,T,d] permuted rows in the compute format (fp32: rows are read in place; q_p not for bf16
+                             without a backward: the kernel fetches its own queries)
     q_idx, k_idx             [S,T] original positions of the permuted rows
     q_sort_key, k_sort_key   [S,T] sort keys, q_off, k_off [S,nb+1] bucket offsets (hash)
     n_q, n_k                 [S] kept counts (QK-dropping)
