@@ -341,11 +341,9 @@ int scfa_qkdrop_attn_fwd(const void *q_c, const void *k_c, const void *v_c,
  * q_perm, k_perm, v_perm, sm_scale as in the forward: the scores are recomputed from the same
  * exact products and scaled per element in fp32.  dtype: SCFA_BF16 only.
  * Range of the backward (beyond it the gradients of the rows concerned are NON-FINITE, not
- * finite and wrong): |LSE| / tau must stay below 2.09e6 (logits of +-2.6e5 at tau = 1/8); per query the kernels hold
- * D / 2^e, with 2^e the power of two that brings the largest |dO| of the row into [1, 2), as a sum of three fp16
- * numbers, which reach 65504 (|D| / 2^e <= 2 d max|O|: |O| in the hundreds); a row of zeros in dO has neither limit;
- * dS = P (dP - D) is formed in fp16: |<dO_i, V_j> - D_i| must stay below 65504, i.e. |V| in the
- * hundreds at the least.  A softmax that is one-hot to fp32 precision (logits in the tens of
+ * finite and wrong): |LSE| / tau must stay below 2.09e6 (logits of +-2.6e5 at tau = 1/8), but for rows of zeros in dO;
+ * dS = P (dP - D) is an fp16 number: with dO scaled so that the largest magnitude of the rows that a sum takes lies in
+ * [1, 2), P_ij |<dO_i, V_j> - D_i| must stay below 65504, i.e. |V| in the hundreds at the least.  A softmax that is one-hot to fp32 precision (logits in the tens of
  * thousands) has dS = P (dP - D) with dP = D up to rounding: its gradients are cancellation
  * noise of relative size 2^-11 against |dO| |V| |K| tau, not against their own (vanishing) size.
  *

@@ -116,18 +116,18 @@ static int attn_bwd_impl(const void* q, const void* k, const void* v, const uint
     unsigned char* w = reinterpret_cast<unsigned char*>(ws);
     void* do_perm = w;
     w += align_up((size_t)S * T * d * 2, 256);
-    void* row_perm = w;                         // [S,T,4] fp32: LSE, D, the row's power of two, 0
+    void* row_perm = w;                         // [S,T,4] fp32: LSE, D, the block's power of two, the row's below it
     w += align_up((size_t)S * T * 16, 256);
     void* aux_perm = w;                         // [S,T,8] fp16: pieces of LSE log2 e and D
     w += align_up((size_t)S * T * 16, 256);
-    int32_t* exp_max = reinterpret_cast<int32_t*>(w);   // [S, bwd_exp_entries(T)] exponents of dO
+    void* row_stats = w;                        // bwd_row_stats_bytes: ranges of dO and D by row block
 
-    rc = launch_bwd_prep_bf16(o, o_f16, lse, d_o, q_key, qkdrop ? n_q : nullptr, S, T, d, sm_scale, do_perm, row_perm, aux_perm, exp_max, st);
+    rc = launch_bwd_prep_bf16(o, o_f16, lse, d_o, q_key, qkdrop ? n_q : nullptr, S, T, d, sm_scale, do_perm, row_perm, aux_perm, row_stats, st);
     if (rc != SCFA_OK) return rc;
     // The rows of dropped tokens (QK-dropping) are zeroed by the two gradient kernels themselves, next to their own stores:
     // as launches of their own in front of the pre-pass, half a gigabyte of fresh zeros on its way out of the caches halved
     // the pace of the pre-pass's streaming reads, and anywhere on this stream they would run with nothing beside them.
-    return launch_attn_bwd_bf16(q, k, v, do_perm, aux_perm, row_perm, exp_max, q_key, k_key, fwd_work, n_fwd, bwd_work, n_bwd,
+    return launch_attn_bwd_bf16(q, k, v, d_o, do_perm, aux_perm, row_perm, row_stats, q_key, k_key, fwd_work, n_fwd, bwd_work, n_bwd,
                                 S, T, d, sm_scale, flags & SCFA_FLAG_STRICT_CAUSAL, dq, dk, dv, qkdrop ? n_q : nullptr,
                                 qkdrop ? n_k : nullptr, st);
 }
@@ -384,7 +384,7 @@ size_t scfa_attn_bwd_workspace_bytes(int S, int T, int d, int dtype)
 {
     if (S <= 0 || T <= 0 || d <= 0 || dtype != SCFA_BF16) return 0;
     return align_up((size_t)S * T * d * 2, 256) + 2 * align_up((size_t)S * T * 16, 256) +
-           align_up(sizeof(int32_t) * (size_t)S * bwd_exp_entries(T), 256);
+           align_up(bwd_row_stats_bytes(S, T), 256);
 }
 
 int scfa_hash_attn_bwd(const void* q_perm, const void* k_perm, const void* v_perm, const uint32_t* q_sort_key,

@@ -123,12 +123,12 @@ int launch_attn_fwd_bf16(const void* q, const void* k, const void* v, const uint
                          const uint32_t* k_key, const int32_t* work, int n_work, int S, int T, int d,
                          float tau, int strict, void* o, float* lse, void* o_f16, const int32_t* n_keep_q, bool own_q, void* q_out,
                          hipStream_t st);   // own_q: q in original order, its permuted copy goes to q_out (nullable); n_keep_q: QK-dropping (the kernel writes the dropped rows), else null
-int bwd_exp_entries(int T);          // entries of exp_max per segment
+size_t bwd_row_stats_bytes(int S, int T);
 int launch_bwd_prep_bf16(const void* o, const void* o_f16, const float* lse, const void* d_o, const uint32_t* q_key,
                          const int32_t* n_q, int S, int T, int d, float tau, void* do_perm, void* row_perm,
-                         void* aux_perm, int32_t* exp_max, hipStream_t st);
-int launch_attn_bwd_bf16(const void* q, const void* k, const void* v, const void* do_perm, const void* aux_perm,
-                         const void* row_perm, const int32_t* exp_max, const uint32_t* q_key,
+                         void* aux_perm, void* row_stats, hipStream_t st);
+int launch_attn_bwd_bf16(const void* q, const void* k, const void* v, const void* d_o, const void* do_perm, const void* aux_perm,
+                         const void* row_perm, const void* row_stats, const uint32_t* q_key,
                          const uint32_t* k_key, const int32_t* fwd_work, int n_fwd, const int32_t* bwd_work, int n_bwd, int S, int T,
                          int d, float tau, int strict, float* dq, float* dk, float* dv, const int32_t* n_keep_q,
                          const int32_t* n_keep_k, hipStream_t st);   // n_keep_*: QK-dropping (the kernels zero the dropped rows), else null

@@ -106,12 +106,46 @@ __device__ __forceinline__ float half_sum(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// op over all lanes of the wavefront, in registers (a shuffle through LDS is ten times the latency of a step)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+template <typename F>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t x, F op)
+{
+    x = op(x, dpp<0xB1>(x));    // quad_perm [1,0,3,2]
+    x = op(x, dpp<0x4E>(x));    // quad_perm [2,3,0,1]
+    x = op(x, dpp<0x141>(x));   // row_half_mirror
+    x = op(x, dpp<0x140>(x));   // row_mirror
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = op(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return op(b[0], b[1]);
+}
+using u16x2 = uint16_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t max_u32(uint32_t a, uint32_t b) { return max(a, b); }
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
 // registers 8*cc .. 8*cc+7 of an accumulator block as an fp16 B-operand chunk; the
 // contraction slots of lane half h are rows { 16*cc + 4h + 0..3, 16*cc + 8 + 4h + 0..3 }
 __device__ __forceinline__ f16x8 pack_chunk(const f32x16& p, int cc)
 {
     return as_f16x8(make_uint4(pack_f16(p[8 * cc + 0], p[8 * cc + 1]), pack_f16(p[8 * cc + 2], p[8 * cc + 3]),
                                pack_f16(p[8 * cc + 4], p[8 * cc + 5]), pack_f16(p[8 * cc + 6], p[8 * cc + 7])));
+}
+
+// the same rounded to nearest: beyond the fp16 range the result is infinite
+__device__ __forceinline__ f16x8 round_chunk(const f32x16& p, int cc)
+{
+    f16x8 r;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = (_Float16)p[8 * cc + e];
+    return r;
 }
 
 // ---------------------------------------------------------------------------
