@@ -431,7 +431,7 @@ int scfa_backward(int variant, const void *fwd_ws, const void *o, const float *l
 #define SCFA_K_BWD_PREP    5
 #define SCFA_K_BWD_DKDV    6
 #define SCFA_K_BWD_DQ      7
-#define SCFA_K_FILL        8
+#define SCFA_K_FILL        8   /* no kernel: the attention kernels write the rows of dropped tokens themselves */
 #define SCFA_K_LSH         9
 #define SCFA_K_COUNT       10
 

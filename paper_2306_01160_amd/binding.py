@@ -25,6 +25,7 @@ SCFA_FLAG_STRICT_CAUSAL = 1
 SCFA_WORK_STRIDE = 8
 # fields of a scfa_forward workspace, in the order of its offsets
 FWD_FIELDS = ("q_key", "k_key", "q_off", "k_off", "work", "bwd_work", "counters", "q_perm", "k_perm", "v_perm", "o_f16")
+# "fill" counts no launch (the attention kernels write the rows of dropped tokens); the numbers stay
 KERNEL_IDS = {"sort": 0, "compact": 1, "gather": 2, "ranges": 3, "fwd": 4, "bwd_prep": 5,
               "bwd_dkdv": 6, "bwd_dq": 7, "fill": 8, "lsh": 9}
 

@@ -1,5 +1,5 @@
 """fp32 forward at the edges of its tiles: query tiles of 64 rows (two wavefronts of 32), key tiles of 32 walked by
-four (d = 64) or two (d = 128) key splits that are put together at the end.
+two key splits that are put together at the end.
 
 Tolerance: fp32 rounding of sums of at most 257 terms of O(1), as for the fp32 path elsewhere (1e-4 on O, 1e-5 on LSE)."""
 import pytest
