@@ -52,3 +52,58 @@ def test_finite_numbers_whose_score_ends_the_range(q5, k5, pos, need_bwd):
     assert torch.equal(torch.isfinite(lse), some) and torch.isfinite(o).all()
     assert float((o - o_ref).abs().max()) < 5e-6
     assert float(((lse - lse_ref)[some].abs() / lse_ref[some].abs().clamp(min=1.0)).max()) < 1e-5
+
+
+def _numbers(S, e):
+    """fp32 numbers of all 24 bits and both signs, those of segment s of magnitude 2^e[s] to 2^(e[s] + 1)"""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    x = 1 + torch.rand((1, S, 1, 64), device="cuda", generator=gen)
+    x *= torch.randint(0, 2, x.shape, device="cuda", generator=gen) * 2 - 1
+    return torch.ldexp(x.double(), torch.tensor(e, device="cuda").view(1, -1, 1, 1)).float()
+
+
+# through fp32's denormals, and around 2^-110 and 2^60, between which numbers are split
+EXPONENTS = (-149, -141, -134, -133, -127, -126, -119, -112, -111, -110, -109, -64, -1, 0, 58, 59, 60, 61, 100, 126)
+
+
+@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("what", ["v", "k", "q"])
+def test_one_key_a_row_gives_back_the_bits(what, need_bwd):
+    """A row of one key: P = 1, so O is V, and the logsumexp is TAU times the one product that is not zero; all exact."""
+    S = len(EXPONENTS)
+    x, label = _numbers(S, EXPONENTS), torch.zeros((1, S, 1), device="cuda", dtype=torch.int32)
+    unit = torch.zeros_like(x)
+    unit[..., 7] = 1.0
+    q, k, v = {"v": (unit, unit, x), "k": (unit, x, unit), "q": (x, unit, unit)}[what]
+    o, lse, _ = pipeline.hash_forward(q, k, v, label, label, 1, TAU, need_bwd=need_bwd)
+    assert torch.equal(o, v)
+    assert torch.equal(lse, unit[..., 7] * TAU if what == "v" else x[..., 7] * TAU)
+
+
+@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("e", [-90, -108, -112, -118, -124])
+def test_small_columns_beside_ordinary_ones_keep_their_bits(e, need_bwd):
+    """By column: 300 sums of products whose roundings are 2^-24 each come to a few 2^-24 of the column's norm, unless the last
+    pieces are missing (2^-118: 2^-17 of the norm; the results keep 24 bits down to 2^-126, of values some 2^4 larger)."""
+    nb = 2
+    q, k, v, lq, lk = _inputs(300, nb)
+    small = [3, 40, 63]
+    v[..., small] = torch.ldexp(v[..., small].double(), torch.tensor(e, device="cuda")).float()
+    o, _, _ = pipeline.hash_forward(q, k, v, lq, lk, nb, TAU, need_bwd=need_bwd)
+    o_ref, _ = _reference(q, k, v, _allowed(lq, lk))
+    assert float(((o - o_ref).norm(dim=2) / o_ref.norm(dim=2)).max()) <= 2.0**-21
+
+
+@pytest.mark.parametrize("need_bwd", [False, True])
+def test_small_elements_of_one_key_keep_their_bits(need_bwd):
+    """One element of a value of which a single row of one key is made; and of a key and a query, whose product is all of a score."""
+    q, k, v, lq, lk = _inputs(65, 65)
+    lq[..., :] = lk[..., :] = torch.arange(65, device="cuda", dtype=torch.int32)       # every row has its own key only
+    tiny = 1.2345678 * 2.0**-118
+    v[:, :, 33, 9] = tiny
+    q[:, :, 34], k[:, :, 34] = 0.0, 0.0
+    q[:, :, 34, 2], k[:, :, 34, 2] = 1.0, tiny
+    o, lse, _ = pipeline.hash_forward(q, k, v, lq, lk, 65, TAU, need_bwd=need_bwd)
+    assert torch.equal(o, v)
+    assert torch.equal(lse[..., 34], torch.full_like(lse[..., 34], tiny) * TAU)
