@@ -107,3 +107,26 @@ def test_small_elements_of_one_key_keep_their_bits(need_bwd):
     o, lse, _ = pipeline.hash_forward(q, k, v, lq, lk, 65, TAU, need_bwd=need_bwd)
     assert torch.equal(o, v)
     assert torch.equal(lse[..., 34], torch.full_like(lse[..., 34], tiny) * TAU)
+
+
+@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("e", [0, 50, -50])
+def test_small_probabilities_keep_their_bits(e, need_bwd):
+    """Column c of the result is one probability between 2^-125 and 2^-90 times one value: key c's, the others are zero there.  The
+    exponent's roundings (the factor TAU log2(e) and the product with it, 3 of 2^-24 of 125) come to 1.6e-5 of a probability; at
+    2^-125 one without its last two pieces is off by 2e-3."""
+    T = 32                                     # one tile of keys, which has one maximum
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T)
+    x = torch.linspace(90.0, 125.0, T, device="cuda")
+    q, k, v = (torch.zeros((1, 2, T, 64), device="cuda") for _ in range(3))
+    q[..., 0] = 1.0
+    k[..., 0] = -x / (TAU * math.log2(math.e))
+    k[:, :, 0] = 0.0                           # the row's maximum: a score of 0
+    v[..., :T] = torch.diag(torch.ldexp(1 + torch.rand(T, device="cuda", generator=gen), torch.tensor(e, device="cuda")))
+    label = torch.zeros((1, 2, T), device="cuda", dtype=torch.int32)
+    o, _, _ = pipeline.hash_forward(q, k, v, label, label, 1, TAU, need_bwd=need_bwd)
+    o_ref, _ = _reference(q, k, v, _allowed(label, label))
+    some = o_ref.abs() > 2.0**-126             # of the others a product has lost bits, in fp32 too
+    assert float(((o - o_ref).abs() / o_ref.abs())[some].max()) < 2e-5
+    assert float(o[~some].abs().max()) <= 2.0**-126
