@@ -130,3 +130,24 @@ def test_small_probabilities_keep_their_bits(e, need_bwd):
     some = o_ref.abs() > 2.0**-126             # of the others a product has lost bits, in fp32 too
     assert float(((o - o_ref).abs() / o_ref.abs())[some].max()) < 2e-5
     assert float(o[~some].abs().max()) <= 2.0**-126
+
+
+# relative error of O (2-norm) with the fp32 instructions, by the share of the inputs that is not zero
+ERROR_OF_FP32_PRODUCTS = {(1536, 1): {1.0: 3.06e-7, 0.5: 1.58e-7, 0.1: 9.06e-8, 0.03: 7.58e-8},
+                          (2048, 8): {1.0: 2.25e-7, 0.5: 1.04e-7, 0.1: 6.97e-8, 0.03: 6.27e-8}}
+
+
+@pytest.mark.parametrize("T,nb", list(ERROR_OF_FP32_PRODUCTS))
+@pytest.mark.parametrize("share", [1.0, 0.5, 0.1, 0.03])
+def test_the_error_is_no_larger_than_with_fp32_products(T, nb, share):
+    """Mean over 16 segments, whose own errors differ by a few per cent."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T)
+    q, k, v = (torch.randn((1, 16, T, 64), device="cuda", generator=gen) * (torch.rand((1, 16, T, 64), device="cuda", generator=gen) < share)
+               for _ in range(3))
+    label = torch.randint(0, nb, (1, 16, T), device="cuda", generator=gen, dtype=torch.int32)
+    o, _, _ = pipeline.hash_forward(q, k, v, label, label, nb, TAU, need_bwd=False)
+    o_ref, _ = _reference(q, k, v, _allowed(label, label))
+    error = float(((o - o_ref).norm(dim=(2, 3)) / o_ref.norm(dim=(2, 3))).mean())
+    print(f"{T} {nb} {share}: {error:.3e}")
+    assert error <= 1.03 * ERROR_OF_FP32_PRODUCTS[T, nb][share]
