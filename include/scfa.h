@@ -444,6 +444,10 @@ int scfa_prof_read(int kernel_id, double *total_ms, int *launches);
  * head dimension d) that one compute unit of the current device holds at once, as the HIP
  * runtime computes it from the kernel's registers and LDS (host out-pointer). */
 int scfa_prof_occupancy(int kernel_id, int d, int *workgroups_per_cu);
+/* Whether scfa_forward with these sizes runs its sort, its schedule and the attention in one launch
+ * (1) or in launches of their own (0; always while the timers are on).  Host arithmetic, no GPU
+ * call; host out-pointer. */
+int scfa_prof_forward_in_one(int variant, int S, int T, int d, int nb, int dtype, int need_bwd, int *in_one);
 
 #ifdef __cplusplus
 }

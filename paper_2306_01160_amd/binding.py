@@ -37,6 +37,7 @@ EXPORTS = [
     "scfa_attn_bwd_workspace_bytes", "scfa_sort_workspace_bytes", "scfa_hash_attn_bwd", "scfa_qkdrop_attn_bwd",
     "scfa_forward_workspace", "scfa_forward", "scfa_backward",
     "scfa_prof_enable", "scfa_prof_reset", "scfa_prof_read", "scfa_prof_occupancy",
+    "scfa_prof_forward_in_one",
 ]
 
 
@@ -87,6 +88,7 @@ def lib():
         L.scfa_prof_enable.argtypes = [ci]
         L.scfa_prof_read.argtypes = [ci, ctypes.POINTER(ctypes.c_double), ip]
         L.scfa_prof_occupancy.argtypes = [ci, ci, ip]
+        L.scfa_prof_forward_in_one.argtypes = [ci, ci, ci, ci, ci, ci, ci, ip]
         for name in EXPORTS:
             fn = getattr(L, name)
             if name not in ("scfa_error_string", "scfa_attn_bwd_workspace_bytes", "scfa_sort_workspace_bytes"):
@@ -405,6 +407,13 @@ def scfa_prof_occupancy(kernel: str, d: int) -> int:
     n = ctypes.c_int(0)
     _check(lib().scfa_prof_occupancy(KERNEL_IDS[kernel], int(d), ctypes.byref(n)), "scfa_prof_occupancy")
     return n.value
+
+
+def scfa_prof_forward_in_one(variant: int, S: int, T: int, d: int, nb: int, dtype: int, need_bwd: bool) -> bool:
+    """Whether a whole-pass forward of these sizes sorts, schedules and attends in one launch."""
+    n = ctypes.c_int(0)
+    _check(lib().scfa_prof_forward_in_one(variant, S, T, d, nb, dtype, int(need_bwd), ctypes.byref(n)), "scfa_prof_forward_in_one")
+    return bool(n.value)
 
 
 def scfa_prof_read(kernel: str):

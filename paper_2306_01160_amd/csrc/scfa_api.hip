@@ -421,6 +421,11 @@ int scfa_forward_workspace(int variant, int S, int T, int d, int nb, int dtype, 
     return SCFA_OK;
 }
 
+static bool forward_in_one(int variant, int S, int T, int d, int nb, int dtype, bool need_bwd, int n_fwd)
+{
+    return dtype == SCFA_F32 && !need_bwd && !prof_enabled() && f32_in_one(variant, S, T, d, nb, n_fwd);
+}
+
 int scfa_forward(int variant, const void* q, const void* k, const void* v, const void* label_q, const void* label_k, int B, int H,
                  int T, int d, int nb, int dtype, float sm_scale, int flags, int need_bwd, void* o_out, float* lse_out, void* ws,
                  size_t ws_bytes, void* stream)
@@ -455,7 +460,7 @@ int scfa_forward(int variant, const void* q, const void* k, const void* v, const
     // buckets 378 -> 372 us a step, but 36 x 5003 rows in 32 uneven buckets 181.8 -> 182.9 and 192 x 1024 in 16 168 -> 169.
     const bool own_q = dtype == SCFA_BF16 && (!need_bwd || (long long)T >= 256LL * nb);
     const int32_t *qi = (const int32_t*)q_key, *ki = (const int32_t*)k_key;
-    if (f32 && !bwd_work && !prof_enabled() && f32_in_one(variant, S, T, d, nb, L.n_fwd))
+    if (forward_in_one(variant, S, T, d, nb, dtype, bwd_work != nullptr, L.n_fwd))
         return launch_f32_one(variant, (const float*)q, (const float*)k, (const float*)v, label_q, label_k, S, T, d, nb, L.n_fwd, sm_scale,
                               strict, q_key, k_key, q_off, k_off, fwd_work, counters, (float*)o_out, lse_out, st);
     // the passes in between go by the sort keys (a compacted index vector is its own key): no index vector is written
@@ -511,6 +516,16 @@ int scfa_prof_occupancy(int kernel_id, int d, int* workgroups_per_cu)
     if (kernel_id == SCFA_K_BWD_DKDV) return occupancy_attn_bwd_dkdv_bf16(d, workgroups_per_cu);
     if (kernel_id == SCFA_K_BWD_DQ) return occupancy_attn_bwd_dq_bf16(d, workgroups_per_cu);
     return SCFA_EUNSUPPORTED;
+}
+
+int scfa_prof_forward_in_one(int variant, int S, int T, int d, int nb, int dtype, int need_bwd, int* in_one)
+{
+    if (!in_one) return SCFA_EINVAL;
+    ForwardLayout L;
+    const int rc = forward_layout(variant, S, T, d, nb, dtype, need_bwd != 0, L);
+    if (rc != SCFA_OK) return rc;
+    *in_one = forward_in_one(variant, S, T, d, nb, dtype, need_bwd != 0, L.n_fwd) ? 1 : 0;
+    return SCFA_OK;
 }
 
 int scfa_prof_enable(int on)
