@@ -234,6 +234,7 @@ template <int WAVES, int STEPS, bool KEEP_MODE, bool TWO>
 __device__ __forceinline__ void sort_side(const void* __restrict__ keys, size_t seg, int T, int nb, int nbits, int wave, int lane,
                                           int32_t* hist, int32_t* off, uint32_t* sorted)
 {
+    static_assert(TWO || !KEEP_MODE, "without TWO the sorted words are sort keys");
     const int ht = wave * 64 + lane;
     int run = (T + WAVES - 1) / WAVES;
     run = (run + 63) & ~63;
