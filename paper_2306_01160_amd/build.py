@@ -28,8 +28,9 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # keep MFMA accumulators in VGPRs (no accumulation-register copies around the softmax)
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
-    # no kernel forms a NaN on purpose (masked scores are -inf, never inf - inf); this lets
-    # max/min skip the quieting of signalling NaNs
+    # no kernel forms a NaN whose value it uses (masked scores are -inf, never inf - inf; the pieces of an infinite
+    # fp32 number are, and its item is left to kernel code without pieces); this lets max/min skip the quieting of
+    # signalling NaNs.  Where an input may be one, its bits are tested, behind an empty asm that hides them.
     "-fno-honor-nans",
     "-Wall", "-Wno-unused-function",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,

@@ -186,8 +186,10 @@ __global__ __launch_bounds__(SORT_THREADS) void stable_sort_small_keys_kernel(
 
 // n_problems: 1 or 2 (bucket1 etc. ignored for 1)
 // Chunks per segment for n_wg = segments x problems workgroups: enough to fill the chip once, but
-// chunks of at least 4096 tokens; 1 for short sequences.  Host arithmetic; the workspace query and
-// the launchers must agree.
+// chunks of at least 4096 tokens; 1 for short sequences.  Host arithmetic.  The workspace query goes by
+// this, and so do the launches that use the workspace (with the counting kernel) and those of 8192 tokens and
+// more.  Below, where the sort kernel counts the other chunks itself and needs no workspace, launch_sort_t
+// takes shorter chunks.
 int sort_chunks(int n_wg, int T)
 {
     if (T < 8192) return 1;

@@ -227,9 +227,10 @@ __device__ __forceinline__ void build_list(bool forward, int strict, const int32
 // Stable sort of T <= 64 * STEPS * WAVES tokens by WAVES wavefronts, the scheme of scfa_index.hip in one workgroup; the other
 // half of the workgroup runs the same steps (barriers) on the other side.  off[0 .. nb]: start of every key; sorted: sort keys
 // (KEEP_MODE: positions).  hist: [WAVES][nb].
-// With two keys 64 atomics on their counters are served nearly one after the other, and a ballot ranks a step: up to two keys (TWO) are
-// ranked while they are counted (one bucket of 4096 rows, forward 58.4 -> 51.8 us; two of 1024 rows, step 41.2 -> 40.3; QK-dropping training step at 32 x 2048 rows 71.2 -> 69.3 us, this launch 12.9 -> 11.3).  With more keys the
-// atomics are the cheaper count (hash forward in fp32, 256 rows in 4 buckets: 17.8 -> 18.0 us ranked at once).
+// With two keys 64 atomics on their counters are served nearly one after the other, and a ballot ranks a step: up to two keys (TWO)
+// are ranked while they are counted (one bucket of 4096 rows, forward 58.4 -> 51.8 us; QK-dropping training step at 32 x 2048 rows
+// 71.2 -> 69.3 us, this launch 12.9 -> 11.3).  With more keys the atomics are the cheaper count (hash forward in fp32, 256 rows in 4
+// buckets: 17.8 -> 18.0 us ranked at once).
 template <int WAVES, int STEPS, bool KEEP_MODE, bool TWO>
 __device__ __forceinline__ void sort_side(const void* __restrict__ keys, size_t seg, int T, int nb, int nbits, int wave, int lane,
                                           int32_t* hist, int32_t* off, uint32_t* sorted)
