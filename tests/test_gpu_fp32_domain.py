@@ -4,7 +4,7 @@ import math
 import pytest
 import torch
 
-from paper_2306_01160_amd import pipeline
+from paper_2306_01160_amd import binding, pipeline
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +18,20 @@ def _reference(q, k, v, allowed):
     lse = torch.logsumexp(s, -1)
     p = torch.where(torch.isneginf(s), 0.0, torch.exp(s - lse.clamp(min=-1e300)[..., None]))
     return torch.matmul(p, v.double()), lse
+
+
+ROUTES = ("in one launch", "sorted apart", "single passes")
+
+
+def _forward(route, q, k, v, lq, lk, nb):
+    """At these sizes a forward shares its launch with its sort, unless it is for a backward; the single passes take permuted rows."""
+    if route != "single passes":
+        return pipeline.hash_forward(q, k, v, lq, lk, nb, TAU, need_bwd=route == "sorted apart")[:2]
+    q, k, v, lq, lk = (x.flatten(0, 1) for x in (q, k, v, lq, lk))
+    (qi, _, qo, qk), (ki, _, ko, kk) = binding.scfa_sort_by_bucket_pair(lq, lk, nb, want_sorted=False)
+    tiles = binding.scfa_tile_config(q.shape[-1], binding.SCFA_F32)
+    work, _, _ = binding.scfa_block_ranges(binding.SCFA_HASH, qi, ki, qo, ko, nb, tiles, want_bwd=False)
+    return binding.scfa_hash_attn_fwd(*binding.scfa_gather_qkv(q, k, v, qi, ki), qk, kk, work, 1, q.shape[0], TAU)
 
 
 def _inputs(T, nb):
@@ -34,11 +48,10 @@ def _allowed(lq, lk):
     return (lq[..., :, None] == lk[..., None, :]) & (at[:, None] >= at[None, :])
 
 
-# a forward for a backward sorts in a launch of its own; the other shares its launch with the attention at these sizes
-@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("pos", [0, 40])
 @pytest.mark.parametrize("q5,k5", [(2005.0, -3e38), (1.004, 3.385e38), (1.004, -3.385e38)])
-def test_finite_numbers_whose_score_ends_the_range(q5, k5, pos, need_bwd):
+def test_finite_numbers_whose_score_ends_the_range(q5, k5, pos, route):
     """One score beyond fp32's range, or so near its end that the product of the leading pieces is beyond it."""
     nb = 2
     q, k, v, lq, lk = _inputs(300, nb)
@@ -46,7 +59,7 @@ def test_finite_numbers_whose_score_ends_the_range(q5, k5, pos, need_bwd):
     q[..., 5] = q5
     k[..., 5] = 0.0
     k[:, :, pos, 5] = k5
-    o, lse, _ = pipeline.hash_forward(q, k, v, lq, lk, nb, TAU, need_bwd=need_bwd)
+    o, lse = _forward(route, q, k, v, lq, lk, nb)
     o_ref, lse_ref = _reference(q, k, v, _allowed(lq, lk))
     some = torch.isfinite(lse_ref)
     assert torch.equal(torch.isfinite(lse), some) and torch.isfinite(o).all()
@@ -67,36 +80,36 @@ def _numbers(S, e):
 EXPONENTS = (-149, -141, -134, -133, -127, -126, -119, -112, -111, -110, -109, -64, -1, 0, 58, 59, 60, 61, 100, 126)
 
 
-@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("what", ["v", "k", "q"])
-def test_one_key_a_row_gives_back_the_bits(what, need_bwd):
+def test_one_key_a_row_gives_back_the_bits(what, route):
     """A row of one key: P = 1, so O is V, and the logsumexp is TAU times the one product that is not zero; all exact."""
     S = len(EXPONENTS)
     x, label = _numbers(S, EXPONENTS), torch.zeros((1, S, 1), device="cuda", dtype=torch.int32)
     unit = torch.zeros_like(x)
     unit[..., 7] = 1.0
     q, k, v = {"v": (unit, unit, x), "k": (unit, x, unit), "q": (x, unit, unit)}[what]
-    o, lse, _ = pipeline.hash_forward(q, k, v, label, label, 1, TAU, need_bwd=need_bwd)
+    o, lse = _forward(route, q, k, v, label, label, 1)
     assert torch.equal(o, v)
     assert torch.equal(lse, unit[..., 7] * TAU if what == "v" else x[..., 7] * TAU)
 
 
-@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("e", [-90, -108, -112, -118, -124])
-def test_small_columns_beside_ordinary_ones_keep_their_bits(e, need_bwd):
+def test_small_columns_beside_ordinary_ones_keep_their_bits(e, route):
     """By column: 300 sums of products whose roundings are 2^-24 each come to a few 2^-24 of the column's norm, unless the last
     pieces are missing (2^-118: 2^-17 of the norm; the results keep 24 bits down to 2^-126, of values some 2^4 larger)."""
     nb = 2
     q, k, v, lq, lk = _inputs(300, nb)
     small = [3, 40, 63]
     v[..., small] = torch.ldexp(v[..., small].double(), torch.tensor(e, device="cuda")).float()
-    o, _, _ = pipeline.hash_forward(q, k, v, lq, lk, nb, TAU, need_bwd=need_bwd)
+    o, _ = _forward(route, q, k, v, lq, lk, nb)
     o_ref, _ = _reference(q, k, v, _allowed(lq, lk))
     assert float(((o - o_ref).norm(dim=2) / o_ref.norm(dim=2)).max()) <= 2.0**-21
 
 
-@pytest.mark.parametrize("need_bwd", [False, True])
-def test_small_elements_of_one_key_keep_their_bits(need_bwd):
+@pytest.mark.parametrize("route", ROUTES)
+def test_small_elements_of_one_key_keep_their_bits(route):
     """One element of a value of which a single row of one key is made; and of a key and a query, whose product is all of a score."""
     q, k, v, lq, lk = _inputs(65, 65)
     lq[..., :] = lk[..., :] = torch.arange(65, device="cuda", dtype=torch.int32)       # every row has its own key only
@@ -104,14 +117,14 @@ def test_small_elements_of_one_key_keep_their_bits(need_bwd):
     v[:, :, 33, 9] = tiny
     q[:, :, 34], k[:, :, 34] = 0.0, 0.0
     q[:, :, 34, 2], k[:, :, 34, 2] = 1.0, tiny
-    o, lse, _ = pipeline.hash_forward(q, k, v, lq, lk, 65, TAU, need_bwd=need_bwd)
+    o, lse = _forward(route, q, k, v, lq, lk, 65)
     assert torch.equal(o, v)
     assert torch.equal(lse[..., 34], torch.full_like(lse[..., 34], tiny) * TAU)
 
 
-@pytest.mark.parametrize("need_bwd", [False, True])
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("e", [0, 50, -50])
-def test_small_probabilities_keep_their_bits(e, need_bwd):
+def test_small_probabilities_keep_their_bits(e, route):
     """Column c of the result is one probability between 2^-125 and 2^-90 times one value: key c's, the others are zero there.  The
     exponent's roundings (the factor TAU log2(e) and the product with it, 3 of 2^-24 of 125) come to 1.6e-5 of a probability; at
     2^-125 one without its last two pieces is off by 2e-3."""
@@ -125,7 +138,7 @@ def test_small_probabilities_keep_their_bits(e, need_bwd):
     k[:, :, 0] = 0.0                           # the row's maximum: a score of 0
     v[..., :T] = torch.diag(torch.ldexp(1 + torch.rand(T, device="cuda", generator=gen), torch.tensor(e, device="cuda")))
     label = torch.zeros((1, 2, T), device="cuda", dtype=torch.int32)
-    o, _, _ = pipeline.hash_forward(q, k, v, label, label, 1, TAU, need_bwd=need_bwd)
+    o, _ = _forward(route, q, k, v, label, label, 1)
     o_ref, _ = _reference(q, k, v, _allowed(label, label))
     some = o_ref.abs() > 2.0**-126             # of the others a product has lost bits, in fp32 too
     assert float(((o - o_ref).abs() / o_ref.abs())[some].max()) < 2e-5
