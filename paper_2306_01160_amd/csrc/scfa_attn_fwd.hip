@@ -74,7 +74,7 @@ __device__ __forceinline__ void fill_dropped_rows(const uint32_t* __restrict__ k
     const int sub = (int)threadIdx.x / CPR, c = (int)threadIdx.x % CPR;
     for (long long r = (long long)n_keep + (long long)w * R + sub; r < T; r += (long long)n_wg * R) {
         const size_t pos = seg + (key_seg[r] & KEY_POS_MASK);
-        reinterpret_cast<uint4*>(o + pos * D)[c] = make_uint4(0u, 0u, 0u, 0u);
+        store_stream(reinterpret_cast<uint4*>(o + pos * D) + c, make_uint4(0u, 0u, 0u, 0u));
         if (c == 0) lse[pos] = -INFINITY;
     }
 }
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
                 pk.y = (uint32_t)__builtin_bit_cast(uint16_t, y2) | ((uint32_t)__builtin_bit_cast(uint16_t, y3) << 16);
                 reinterpret_cast<uint2*>(stage.chunk(l32, db * 4 + g))[h] = pk;
             }
-        stage.store(o, n_rows, lane, original);
+        stage.template store<true>(o, n_rows, lane, original);
         if (o_f16) {   // the same values with 11 significant bits, for the backward's D = <dO, O>
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
@@ -477,13 +477,13 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
                     hk.y = (uint32_t)__builtin_bit_cast(uint16_t, z2) | ((uint32_t)__builtin_bit_cast(uint16_t, z3) << 16);
                     reinterpret_cast<uint2*>(stage.chunk(l32, db * 4 + g))[h] = hk;
                 }
-            stage.store(o_f16, n_rows, lane, original);
+            stage.template store<false>(o_f16, n_rows, lane, original);
         }
         if (OWN_Q && q_out) {
 #pragma unroll
             for (int kk = 0; kk < D / 16; ++kk)
                 *reinterpret_cast<uint4*>(stage.chunk(l32, 2 * kk + h)) = __builtin_bit_cast(uint4, qf[b][kk]);
-            stage.store(q_out, n_rows, lane, [&](int row) { return seg + (size_t)(q_begin + (wave * QB + b) * 32 + row); });
+            stage.template store<false>(q_out, n_rows, lane, [&](int row) { return seg + (size_t)(q_begin + (wave * QB + b) * 32 + row); });
         }
     }
 }

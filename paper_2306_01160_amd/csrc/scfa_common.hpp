@@ -66,6 +66,15 @@ constexpr uint32_t KEY_POS_MASK = (1u << KEY_POS_BITS) - 1u;
 constexpr uint32_t KEY_PAST_END = 0xffffffffu;   // rows past the end of a ragged tile: match no range
 constexpr uint32_t KEY_NEVER = 0xfffffffeu;      // lower end of the range of a row that may match nothing
 
+// ---- streams ----------------------------------------------------------------------
+// Sixteen bytes that no kernel of the path reads again.  As ordinary stores the results of a training step (O, the fp32 gradients,
+// zeros of dropped rows: 350 MB at 48 x 8192 x 64 rows) take the place of the permuted copies in L2 and the 256 MB behind it, which
+// the kernels still read: 373 -> 355 us a step there, 36 x 5003 rows 184 -> 176, 192 x 1024 169 -> 161, 24 x 16384 698 -> 678.  Only for
+// instructions that write whole cache lines: smaller pieces are then not put together any more (dK/dV with 32-byte pieces 40 % slower
+// at 24 x 16384 rows, 2.5 times at 48 x 8192).
+typedef unsigned int u32v4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_stream(uint4* p, uint4 x) { __builtin_nontemporal_store(__builtin_bit_cast(u32v4, x), reinterpret_cast<u32v4*>(p)); }
+
 // ---- tile configuration -------------------------------------------------------
 constexpr int FWD_TILE_M = 128;  // query rows per workgroup (4 waves x 32)
 constexpr int FWD_TILE_N = 64;   // keys per inner step

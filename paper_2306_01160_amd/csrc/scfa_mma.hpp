@@ -12,8 +12,7 @@
 // Any assignment of contraction indices to slots is valid as long as A and B agree.
 #pragma once
 
-#include <hip/hip_runtime.h>
-#include <stdint.h>
+#include "scfa_common.hpp"
 
 namespace scfa {
 
@@ -311,8 +310,8 @@ struct AsyncTile {
 // Results of a wavefront (one row per lane, the row's elements in its registers) on their way to memory: a store straight from
 // the registers writes 16 or 32 bytes of 32 different rows per instruction, and the L2 takes one request per piece.  The
 // wavefront lays its 32 rows out in LDS (its own ROW_BYTES x 32, chunks of 16 bytes swizzled) and writes whole rows.
-// (Forward kernel, O, its fp16 copy and the copy of Q, 48 x 8192 rows in 16 buckets, d = 64: 111 -> 96 us.  The gradients'
-// 32-byte pieces of fp32 rows are merged well enough: +1 % to -1 % on the step, left as they are.)
+// (Forward kernel, O, its fp16 copy and the copy of Q, 48 x 8192 rows in 16 buckets, d = 64: 111 -> 96 us.  Gradients, whose pieces
+// are 32 bytes of fp32 rows, same rows: dK/dV 121 -> 115 us, dQ 98 -> 99 us; streamed as well, see store_stream, 114 and 89 us.)
 template <int ROW_BYTES>
 struct RowStage {
     static constexpr int CH = ROW_BYTES / 16;       // chunks per row
@@ -320,8 +319,8 @@ struct RowStage {
     unsigned char* base;                            // this wavefront's region
     __device__ __forceinline__ unsigned char* chunk(int row, int c) const { return base + row * ROW_BYTES + ((c ^ (row & (CH < 16 ? CH - 1 : 15))) << 4); }
     // out + place(row) * ROW_BYTES: where row goes; rows >= n are left out.  Everything staged before is visible (the LDS
-    // operations of a wavefront stay in order).
-    template <typename F>
+    // operations of a wavefront stay in order).  STREAM: see store_stream.
+    template <bool STREAM, typename F>
     __device__ __forceinline__ void store(void* out, int n, int lane, F place) const
     {
         __builtin_amdgcn_wave_barrier();
@@ -330,7 +329,8 @@ struct RowStage {
             const int row = (j * 64 + lane) / CH, c = lane % CH;
             const size_t at = place(row);
             const uint4 x = *reinterpret_cast<const uint4*>(chunk(row, c));
-            if (row < n) reinterpret_cast<uint4*>(static_cast<unsigned char*>(out) + at * ROW_BYTES)[c] = x;
+            uint4* const to = reinterpret_cast<uint4*>(static_cast<unsigned char*>(out) + at * ROW_BYTES) + c;
+            if (row < n) { if (STREAM) store_stream(to, x); else *to = x; }
         }
         __builtin_amdgcn_wave_barrier();
     }
