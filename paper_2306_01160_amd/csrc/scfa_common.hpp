@@ -74,6 +74,7 @@ constexpr uint32_t KEY_NEVER = 0xfffffffeu;      // lower end of the range of a 
 // at 24 x 16384 rows, 2.5 times at 48 x 8192).
 typedef unsigned int u32v4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_stream(uint4* p, uint4 x) { __builtin_nontemporal_store(__builtin_bit_cast(u32v4, x), reinterpret_cast<u32v4*>(p)); }
+__device__ __forceinline__ uint4 load_stream(const uint4* p) { return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32v4*>(p))); }
 
 // ---- tile configuration -------------------------------------------------------
 constexpr int FWD_TILE_M = 128;  // query rows per workgroup (4 waves x 32)

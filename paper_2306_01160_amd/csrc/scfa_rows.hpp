@@ -132,7 +132,9 @@ __device__ __forceinline__ uint4 convert_chunk(uint4 v, float scale)
     return v;
 }
 
-// chunks g0 + i * stride (i < N) of segment s: the N index reads, then the N row reads of a thread are in flight together
+// chunks g0 + i * stride (i < N) of segment s: the N index reads, then the N row reads of a thread are in flight together.  The rows are
+// read past the caches: nobody reads them again (training step, 24 x 16384 rows 675 -> 672 us, 64 x 4096 x 128 457 -> 455,
+// 192 x 1024 161.4 -> 159.8, no slower anywhere).
 template <int MODE, int N>
 __device__ __forceinline__ void gather_chunks(const GatherProblem& pr, int s, long long g0, int stride, int T, int chunks_per_row,
                                               int32_t pos_mask)
@@ -151,7 +153,7 @@ __device__ __forceinline__ void gather_chunks(const GatherProblem& pr, int s, lo
     const int c = (int)(g0 % chunks_per_row);        // the stride is a whole number of rows
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        if (r[i] < n) v[i] = x[(size_t)src[i] * chunks_per_row + c];
+        if (r[i] < n) v[i] = load_stream(x + (size_t)src[i] * chunks_per_row + c);
 #pragma unroll
     for (int i = 0; i < N; ++i)
         if (r[i] < n) out[(size_t)r[i] * chunks_per_row + c] = convert_chunk<MODE>(v[i], pr.scale);
