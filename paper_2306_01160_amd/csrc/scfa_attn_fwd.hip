@@ -115,11 +115,40 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     const int32_t* it = work + ((size_t)s * n_work + w) * WORK_STRIDE;
     const int q_begin = it[W_QBEGIN], q_count = it[W_QCOUNT];
     const int k_begin = it[W_KBEGIN], k_count = it[W_KCOUNT], k_nomask = it[W_KNOMASK];
-    if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + (size_t)s * T, n_keep_q[s], T, w, n_work, o, lse, (size_t)s * T);
-    if (q_count <= 0) return;
+    const size_t seg = (size_t)s * T;
+    if (q_count <= 0) {   // no work: only the share of the dropped rows (n_keep_q: QK-dropping, else null)
+        if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + seg, n_keep_q[s], T, w, n_work, o, lse, seg);
+        return;
+    }
 
     const int tid = threadIdx.x % THREADS, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-    const size_t seg = (size_t)s * T;
+
+    const uint16_t* kbase = k + (seg + k_begin) * D;
+    const uint16_t* vbase = v + (seg + k_begin) * D;
+    const uint32_t* kib = k_key + seg + k_begin;
+    const int n_tiles = (k_count + BN - 1) / BN;
+    const int n_free = k_nomask / BN;            // leading tiles that need no mask
+
+    AsyncTile<D, BN, THREADS> loader;
+    loader.init();
+    const u32x4 k_desc = make_desc(kbase, (uint32_t)k_count * D * 2);
+    const u32x4 v_desc = make_desc(vbase, (uint32_t)k_count * D * 2);
+    const u32x4 p_desc = make_desc(kib, (uint32_t)k_count * 4);
+    // every wavefront issues the same number of loads per tile (BN / NW key positions each), so one
+    // vmcnt threshold serves all; tiles past the end read zeros into a buffer nobody uses
+    auto issue = [&](int jt, int buf) {
+        const uint32_t base = lds0 + (uint32_t)(buf * BUF_BYTES);
+        loader.load(k_desc, jt * loader.TILE_BYTES, base);
+        loader.load(v_desc, jt * loader.TILE_BYTES, base + TILE_ELEMS * 2);
+        if (lane < KPW)
+            async_load4(p_desc, __builtin_amdgcn_readfirstlane(base + TILE_ELEMS * 4 + wave * KPW * 4),
+                        (wave * KPW + lane) * 4, jt * BN * 4);
+    };
+    // the first tiles are on their way while the rows of the item are fetched and looked at: behind them they were one memory latency
+    // more of every item (192 x 1024 rows in 16 buckets 160.5 -> 158.7 us a step, 36 x 8192 272 -> 268; both gradients likewise)
+#pragma unroll
+    for (int u = 0; u < NBUF - 1; ++u) issue(u * KS + group, u);
+    if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + seg, n_keep_q[s], T, w, n_work, o, lse, seg);
 
     int qrow[QB], qpos[QB];
     // a key is allowed iff (its sort key - qlo) <= qspan: same bucket, position <= the query's (< if strict)
@@ -167,35 +196,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
     for (int b = 0; b < QB; ++b)
         if (qlo[b] != KEY_NEVER) { qlo_wave = min(qlo_wave, qlo[b]); qhi_wave = max(qhi_wave, qlo[b] + qspan[b]); }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        qlo_wave = min(qlo_wave, (uint32_t)__shfl_xor((int)qlo_wave, off));
-        qhi_wave = max(qhi_wave, (uint32_t)__shfl_xor((int)qhi_wave, off));
-    }
-    qlo_wave = __builtin_amdgcn_readfirstlane(qlo_wave);
-    qhi_wave = __builtin_amdgcn_readfirstlane(qhi_wave);
-
-    const uint16_t* kbase = k + (seg + k_begin) * D;
-    const uint16_t* vbase = v + (seg + k_begin) * D;
-    const uint32_t* kib = k_key + seg + k_begin;
-    const int n_tiles = (k_count + BN - 1) / BN;
-    const int n_free = k_nomask / BN;            // leading tiles that need no mask
-
-    AsyncTile<D, BN, THREADS> loader;
-    loader.init();
-    const u32x4 k_desc = make_desc(kbase, (uint32_t)k_count * D * 2);
-    const u32x4 v_desc = make_desc(vbase, (uint32_t)k_count * D * 2);
-    const u32x4 p_desc = make_desc(kib, (uint32_t)k_count * 4);
-    // every wavefront issues the same number of loads per tile (BN / NW key positions each), so one
-    // vmcnt threshold serves all; tiles past the end read zeros into a buffer nobody uses
-    auto issue = [&](int jt, int buf) {
-        const uint32_t base = lds0 + (uint32_t)(buf * BUF_BYTES);
-        loader.load(k_desc, jt * loader.TILE_BYTES, base);
-        loader.load(v_desc, jt * loader.TILE_BYTES, base + TILE_ELEMS * 2);
-        if (lane < KPW)
-            async_load4(p_desc, __builtin_amdgcn_readfirstlane(base + TILE_ELEMS * 4 + wave * KPW * 4),
-                        (wave * KPW + lane) * 4, jt * BN * 4);
-    };
+    qlo_wave = __builtin_amdgcn_readfirstlane(wave_reduce(qlo_wave, min_u32));
+    qhi_wave = __builtin_amdgcn_readfirstlane(wave_reduce(qhi_wave, max_u32));
 
     // lane-invariant offsets of the transposing V reads
     int v_off[4][D / 32][2];
@@ -386,8 +388,6 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
         }
     };
 
-#pragma unroll
-    for (int u = 0; u < NBUF - 1; ++u) issue(u * KS + group, u);
     // one step: wait for this wavefront's share of tile jt, mark keys past the end of a ragged
     // tile (always a masked tile), barrier, refill the buffer everyone has just left, compute.
     // With KS groups group g takes tiles g, g + KS, ..., all of them the same number of steps (the barrier is the workgroup's):

@@ -125,6 +125,7 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t x, F op)
 }
 using u16x2 = uint16_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t max_u32(uint32_t a, uint32_t b) { return max(a, b); }
+__device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return min(a, b); }
 __device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
