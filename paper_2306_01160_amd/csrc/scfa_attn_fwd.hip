@@ -206,6 +206,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) swz_trans_offsets<D>(c4 * 16, db * 32, lane, v_off[c4][db][0], v_off[c4][db][1]);
 
+    const bool idle = wave * (QB * 32) >= q_count;   // none of the item's rows: it only loads tiles (scfa_attn_bwd.hip, dkdv_item)
     bool settled = false;   // every row of this wavefront has a finite reference maximum (wave-uniform)
     auto tile = [&](int buf, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
@@ -405,8 +406,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
         issue(jt + (NBUF - 1) * KS, refill);
         // sort keys ascend along the keys of an item: a tile that lies entirely above or entirely
         // below what the queries of this wavefront may attend to contributes nothing to it
-        bool skip = false;
-        if (MASKED)
+        bool skip = idle;
+        if (MASKED && !skip)
             skip = (uint32_t)__builtin_amdgcn_readfirstlane(kpos_tile(cur)[0]) > qhi_wave ||
                    (uint32_t)__builtin_amdgcn_readfirstlane(kpos_tile(cur)[BN - 1]) < qlo_wave;
         if (!skip) tile(cur, masked_tag);
