@@ -107,11 +107,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     auto kpos_tile = [&](int buf) { return reinterpret_cast<uint32_t*>(smem_raw + buf * BUF_BYTES + TILE_ELEMS * 4); };
     const uint32_t lds0 = lds_address(smem_raw);
 
-    // consecutive workgroups take the same work rank of consecutive segments: the longest
-    // items of every segment are dispatched first, and when S is a multiple of 8 a segment
-    // stays on one XCD (its K/V stay in that XCD's L2).
-    const int s = blockIdx.x % S;
-    const int w = first + blockIdx.x / S;
+    int s, w;
+    place_workgroup(blockIdx.x, S, s, w);
+    w += first;
     const int32_t* it = work + ((size_t)s * n_work + w) * WORK_STRIDE;
     const int q_begin = it[W_QBEGIN], q_count = it[W_QCOUNT];
     const int k_begin = it[W_KBEGIN], k_count = it[W_KCOUNT], k_nomask = it[W_KNOMASK];

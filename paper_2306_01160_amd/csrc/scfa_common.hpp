@@ -84,6 +84,23 @@ constexpr int BWD_TILE_M = 64;   // query rows per inner step of the dK/dV kerne
 constexpr int F32_TILE_M = 64;   // fp32 path: query rows per workgroup (2 waves x 32, times the key splits)
 constexpr int F32_TILE_N = 32;   // keys per tile of one wave
 
+// ---- which segment and work rank a workgroup takes ---------------------------------------------
+// Workgroup b of a launch of the fp16 attention kernels takes work rank b / S of a segment: the longest items of every segment are dispatched first.
+// Workgroups go round the 8 XCDs, and the ranks are turned by (b / S) S mod 8 places so that a segment meets the same XCD, and its
+// streams that XCD's L2, at every rank, but for the up to 7 segments at the turn.  (Not up to 8 segments, most of which would be at
+// the turn.)  Training step in us, as they come / turned: 30 x 1500 rows 58.5 / 56.0, 100 x 2000 174.2 / 169.6, 36 x 5003 172.9 / 170.8,
+// 18 x 3500 x 128 147.8 / 145.0, 20 x 8192 147.0 / 144.6, 36 x 8192 261.9 / 261.1; QK-dropping 20 x 1000 51.4 / 49.4, 9 x 20000 551 / 543.
+// (fp32, whose rows are read in place: 30 x 1000 33.2 / 32.9, but 20 x 2000 x 128 97.2 / 98.6: left as they come.)
+__device__ __forceinline__ void place_workgroup(int b, int S, int& s, int& rank)
+{
+    rank = b / S;
+    s = b - rank * S;
+    if (S > 8) {
+        s += (b - s) & 7;
+        if (s >= S) s -= S;
+    }
+}
+
 // ---- grids beyond 2^32 threads ---------------------------------------------------------------
 // A launch whose threads do not fit 32 bits runs only part of its workgroups and reports no error.  The attention kernels take a
 // workgroup per work item and segment, item-major, and the items from `first` on: launch(first, items) is called for as many
