@@ -232,8 +232,7 @@ int scfa_gather_qkv(const void *q, const void *k, const void *v,
  * Buckets with fewer rows than a tile are the exception: consecutive ones are
  * put together into one item (as many whole buckets as fit a tile of the
  * tiled side) that spans all their queries and all their keys; inside such an
- * item every tile takes the bucket and the causal test.  On the other side
- * they may have up to two tiles of rows where S * T > 131072 (bf16 tiles).
+ * item every tile takes the bucket and the causal test.
  *
  * Tile sizes must be the ones scfa_tile_config() reports for (d, dtype).
  *

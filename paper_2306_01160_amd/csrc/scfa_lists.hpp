@@ -67,17 +67,6 @@ __device__ __forceinline__ int order_key(int bucket, int b_count)
     return ((bucket / ORDER_GROUP) << 24) | (0xffffff - min(b_count, 0xffffff));
 }
 
-// Buckets with at least as many rows on the ranged side are not put together with others.  One tile: an item of several walks
-// fewer tiles than an item each would.  Two tiles: it walks as many, most of its wavefronts skip those of the other buckets, and its first loads
-// and stores serve them all; but the longest item of the launch is a tile longer, which is what a launch with few items takes.
-// Training step in us with one tile / two: 192 x 1024 rows in 16 buckets 157.9 / 151.4, 96 x 4096 in 64 294 / 277, 48 x 8192 in 128
-// 295 / 278, 36 x 5003 in 32 uneven 172.7 / 171.4, 100 x 2000 in 20 uneven 166.6 / 165.4;  24 x 4096 x 128 in 60 194 / 189;  30 x 1024
-// in 16 46.1 / 47.0, 180 x 300 in 4 57.9 / 58.9, forward of 100 x 1024 in 16 30.6 / 31.6, of 30 x 1000 in 20 in fp32 22.8 / 25.7.
-__host__ __device__ __forceinline__ int most_joined(int S, int T, int tile_a, int tile_b)
-{
-    return tile_a != F32_TILE_M && (long long)S * T > 131072 ? 2 * tile_b : tile_b;
-}
-
 // Builds one work list.  Latency-bound: a few dependent LDS reads per phase, and the instructions themselves, which come from L2 the
 // first time (one body for both lists and both mask forms: with one each, four in a kernel, the gather in the same launch took 42 us
 // instead of 39 at 32 x 7001 x 128).  The two searches of an item run together and the items of its bucket pair are read off its unit's
@@ -91,12 +80,16 @@ __host__ __device__ __forceinline__ int most_joined(int S, int T, int tile_a, in
 template <int THREADS>
 __device__ __forceinline__ void build_list(bool forward, int strict, const int32_t* __restrict__ a_idx, const Searched& b_idx,
                            const int32_t* a_off, const int32_t* b_off, int nb, int tile_a,
-                           int tile_b, int most_b, int n_items_max, int32_t* __restrict__ work_out,
+                           int tile_b, int n_items_max, int32_t* __restrict__ work_out,
                            long long* counters2, int32_t* s_tile_base, int32_t* s_unit_first, int32_t* s_cost)
 {
-    // Units (nb <= 256): a bucket with a tile or more of rows on the tiled side, or `most_b` on the other (see most_joined), is a
-    // unit of its own (its items keep their causal range and mask-free prefix); consecutive shorter
-    // ones are taken together while their rows on the tiled side fit one tile.
+    // Units (nb <= 256): a bucket with a tile or more of rows on either side is a
+    // unit of its own (its items keep their causal range and mask-free prefix); consecutive buckets
+    // that are shorter than a tile on both sides are taken together while their rows on the tiled
+    // side fit one tile: only there does one item walk fewer tiles than one item per bucket would.
+    // Buckets of up to two tiles on the ranged side stay apart although sharing items is faster (training step of 192 x 1024 rows in
+    // 16 buckets 158 -> 151 us): masked values are multiplied by 0, so a value that is not finite would reach the rows of the
+    // buckets beside its own, and dK / dV would be formed on the scale of the largest dO of them all.
     // Tiles per unit -> exclusive prefix.  The merge is a serial scan over the buckets; one wavefront holds the bucket
     // sizes in its lanes and reads them out as scalars (a scan over LDS by one thread cost its LDS latency three times per
     // bucket: 16 us of schedule at 32 buckets, 72 segments).
@@ -108,7 +101,7 @@ __device__ __forceinline__ void build_list(bool forward, int strict, const int32
         if (nb <= 64) {
             // whether the next bucket could join lane b's; often no neighbours are so short
             const int after = min(lane + 1, nb - 1), ra1 = a_off[after + 1] - a_off[after], rb1 = b_off[after + 1] - b_off[after];
-            if (__ballot(lane < nb - 1 && ra0 < tile_a && max(rb0, rb1) < most_b && ra0 + ra1 <= tile_a) == 0) {
+            if (__ballot(lane < nb - 1 && ra0 < tile_a && max(rb0, rb1) < tile_b && ra0 + ra1 <= tile_a) == 0) {
                 const int n = lane < nb ? (ra0 + tile_a - 1) / tile_a : 0, end = wave_prefix(n);
                 if (lane < nb) { s_unit_first[lane] = lane; s_tile_base[lane] = end - n; }
                 if (lane == nb - 1) { s_unit_first[nb] = nb; s_tile_base[nb] = end; s_n_units = nb; }
@@ -118,12 +111,12 @@ __device__ __forceinline__ void build_list(bool forward, int strict, const int32
                 bool open = false;                 // the unit being built may take further buckets
                 for (int b = 0; b < nb; ++b) {
                     const int ra = __builtin_amdgcn_readlane(ra0, b), rb = __builtin_amdgcn_readlane(rb0, b);
-                    if (open && rb < most_b && rows + ra <= tile_a) {
+                    if (open && rb < tile_b && rows + ra <= tile_a) {
                         rows += ra;
                     } else {
                         firsts |= 1ull << b;
                         rows = ra;
-                        open = ra < tile_a && rb < most_b;
+                        open = ra < tile_a && rb < tile_b;
                     }
                 }
                 const unsigned long long here = 1ull << lane, behind = firsts & ~(here | (here - 1));
@@ -142,7 +135,7 @@ __device__ __forceinline__ void build_list(bool forward, int strict, const int32
                 const int n = min(64, nb - b0);
                 for (int i = 0; i < n; ++i) {
                     const int ra = __builtin_amdgcn_readlane(ra_lane, i), rb = __builtin_amdgcn_readlane(rb_lane, i);
-                    if (open && rb < most_b && rows + ra <= tile_a) {
+                    if (open && rb < tile_b && rows + ra <= tile_a) {
                         rows += ra;
                         continue;
                     }
@@ -150,7 +143,7 @@ __device__ __forceinline__ void build_list(bool forward, int strict, const int32
                     if (threadIdx.x == 0) { s_unit_first[u] = b0 + i; s_tile_base[u] = acc; }
                     ++u;
                     rows = ra;
-                    open = ra < tile_a && rb < most_b;
+                    open = ra < tile_a && rb < tile_b;
                 }
             }
             acc += (rows + tile_a - 1) / tile_a;

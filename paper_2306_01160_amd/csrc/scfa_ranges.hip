@@ -38,7 +38,7 @@ constexpr int RANGES_THREADS = 512;
 struct RangesArgs {
     int variant;
     const int32_t *q_idx, *k_idx, *q_off, *k_off;
-    int S, T, nb, fwd_m, fwd_n, bwd_n, bwd_m, n_fwd, n_bwd, stage_shift, strict;
+    int T, nb, fwd_m, fwd_n, bwd_n, bwd_m, n_fwd, n_bwd, stage_shift, strict;
     int32_t *fwd_work, *bwd_work;
     long long* counters;
 };
@@ -113,8 +113,7 @@ __device__ void ranges_block(const RangesArgs& ar, int s, bool backward, int32_t
     long long* cnt = ar.counters ? ar.counters + (size_t)s * 4 : nullptr;
     if (!backward && !ar.bwd_work && cnt && threadIdx.x == 0) { cnt[2] = 0; cnt[3] = 0; }
     build_list<RANGES_THREADS>(!backward, ar.strict, backward ? ki : qi, searched, backward ? s_koff : s_qoff, backward ? s_qoff : s_koff, nb,
-                               backward ? bwd_n : fwd_m, backward ? bwd_m : fwd_n,
-                               most_joined(ar.S, T, backward ? bwd_n : fwd_m, backward ? bwd_m : fwd_n), backward ? n_bwd : n_fwd,
+                               backward ? bwd_n : fwd_m, backward ? bwd_m : fwd_n, backward ? n_bwd : n_fwd,
                                backward ? ar.bwd_work + (size_t)s * n_bwd * WORK_STRIDE : ar.fwd_work + (size_t)s * n_fwd * WORK_STRIDE,
                                cnt ? cnt + (backward ? 2 : 0) : nullptr, s_tile_base, s_unit_first, s_cost);
 }
@@ -217,7 +216,7 @@ __global__ __launch_bounds__(PREPARE_THREADS) void prepare_kernel(PrepareArgs ar
         long long* cnt = ar.counters + (size_t)s * 4;
         if (ar.n_lists == 1 && threadIdx.x == 0) { cnt[2] = 0; cnt[3] = 0; }
         build_list<PREPARE_THREADS>(fwd, ar.strict, fwd ? qi : ki, Searched{fwd ? ki : qi, fwd ? ki : qi, 0}, fwd ? s_qoff : s_koff, fwd ? s_koff : s_qoff,
-                                    nb, fwd ? ar.fwd_m : BWD_TILE_N, fwd ? ar.fwd_n : BWD_TILE_M, fwd ? ar.fwd_n : BWD_TILE_M, fwd ? ar.n_fwd : ar.n_bwd,
+                                    nb, fwd ? ar.fwd_m : BWD_TILE_N, fwd ? ar.fwd_n : BWD_TILE_M, fwd ? ar.n_fwd : ar.n_bwd,
                                     fwd ? ar.fwd_work + (size_t)s * ar.n_fwd * WORK_STRIDE : ar.bwd_work + (size_t)s * ar.n_bwd * WORK_STRIDE,
                                     cnt + (fwd ? 0 : 2), s_tile_base, s_unit_first, s_cost);
         return;
@@ -308,7 +307,7 @@ int launch_block_ranges(int variant, const int32_t* q_idx, const int32_t* k_idx,
     const size_t smem = ranges_smem(T, nb, n_fwd > n_bwd ? n_fwd : n_bwd, 144 * 1024, shift);
     static std::atomic<unsigned long long> lds_allowed{0};
     { const int rc_ = allow_dynamic_lds(reinterpret_cast<const void*>(&block_ranges_kernel), 144 * 1024, lds_allowed); if (rc_ != SCFA_OK) return rc_; }
-    const RangesArgs ar{variant, q_idx, k_idx, q_off, k_off, S, T, nb, fwd_m, fwd_n, bwd_n, bwd_m, n_fwd, n_bwd, shift, strict,
+    const RangesArgs ar{variant, q_idx, k_idx, q_off, k_off, T, nb, fwd_m, fwd_n, bwd_n, bwd_m, n_fwd, n_bwd, shift, strict,
                         fwd_work, bwd_work, (long long*)counters};
     ProfScope prof(SCFA_K_RANGES, st);
     hipLaunchKernelGGL(block_ranges_kernel, dim3(S, bwd_work ? 2 : 1), dim3(RANGES_THREADS), smem, st, ar);
@@ -327,7 +326,7 @@ int launch_gather_and_ranges(int variant, const void* q, const void* k, const vo
     int shift;
     const int n_max = n_fwd > n_bwd ? n_fwd : n_bwd;
     const size_t smem = ranges_smem(T, nb, n_max, 36 * 1024 + 4 * (size_t)n_max, shift);
-    const RangesArgs ar{variant, q_idx, k_idx, q_off, k_off, S, T, nb, FWD_TILE_M, FWD_TILE_N, BWD_TILE_N, BWD_TILE_M, n_fwd, n_bwd,
+    const RangesArgs ar{variant, q_idx, k_idx, q_off, k_off, T, nb, FWD_TILE_M, FWD_TILE_N, BWD_TILE_N, BWD_TILE_M, n_fwd, n_bwd,
                         shift, strict, fwd_work, bwd_work, (long long*)counters};
     const bool drop = variant == SCFA_QKDROP;
     const GatherBatch batch{{{k, k_idx, drop ? k_off : nullptr, k_p, 1.f}, {v, k_idx, drop ? k_off : nullptr, v_p, 1.f},
