@@ -148,6 +148,25 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     for (int u = 0; u < NBUF - 1; ++u) issue(u * KS + group, u);
     if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + seg, n_keep_q[s], T, w, n_work, o, lse, seg);
 
+    int cur = 0;
+    auto refill_of = [&] { return cur == 0 ? NBUF - 1 : cur - 1; };    // the buffer of the tile before
+    auto mark_end = [&](int jt) {                                      // keys past the end of a ragged tile are never allowed
+        const int key = jt * BN + wave * KPW + lane;
+        if (lane < KPW && key >= k_count) kpos_tile(cur)[wave * KPW + lane] = KEY_PAST_END;
+    };
+    if (wave * (QB * 32) >= q_count) {   // a wavefront without rows only loads (scfa_attn_bwd.hip, dkdv_item)
+        for (int jt = 0; jt < n_tiles; jt += KS) {
+            wait_async<LOADS_PER_TILE * (NBUF - 2)>();
+            mark_end(jt + group);
+            lds_barrier();
+            issue(jt + group + (NBUF - 1) * KS, refill_of());
+            cur = cur == NBUF - 1 ? 0 : cur + 1;
+        }
+        wait_async<0>();
+        for (int i = 0; i < KS; ++i) lds_barrier();
+        return;
+    }
+
     int qrow[QB], qpos[QB];
     // a key is allowed iff (its sort key - qlo) <= qspan: same bucket, position <= the query's (< if strict)
     uint32_t qlo[QB], qspan[QB];
@@ -204,7 +223,6 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) swz_trans_offsets<D>(c4 * 16, db * 32, lane, v_off[c4][db][0], v_off[c4][db][1]);
 
-    const bool idle = wave * (QB * 32) >= q_count;   // none of the item's rows: it only loads tiles (scfa_attn_bwd.hip, dkdv_item)
     bool settled = false;   // every row of this wavefront has a finite reference maximum (wave-uniform)
     auto tile = [&](int buf, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
@@ -391,21 +409,16 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     // tile (always a masked tile), barrier, refill the buffer everyone has just left, compute.
     // With KS groups group g takes tiles g, g + KS, ..., all of them the same number of steps (the barrier is the workgroup's):
     // a tile past the end is all KEY_PAST_END and skipped.
-    int cur = 0;
     auto step = [&](int jt, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         wait_async<LOADS_PER_TILE * (NBUF - 2)>();
-        if (MASKED && lane < KPW) {
-            const int key = jt * BN + wave * KPW + lane;
-            if (key >= k_count) kpos_tile(cur)[wave * KPW + lane] = KEY_PAST_END;   // never allowed
-        }
+        if (MASKED) mark_end(jt);
         lds_barrier();
-        const int refill = cur == 0 ? NBUF - 1 : cur - 1;    // the buffer of the tile before
-        issue(jt + (NBUF - 1) * KS, refill);
+        issue(jt + (NBUF - 1) * KS, refill_of());
         // sort keys ascend along the keys of an item: a tile that lies entirely above or entirely
         // below what the queries of this wavefront may attend to contributes nothing to it
-        bool skip = idle;
-        if (MASKED && !skip)
+        bool skip = false;
+        if (MASKED)
             skip = (uint32_t)__builtin_amdgcn_readfirstlane(kpos_tile(cur)[0]) > qhi_wave ||
                    (uint32_t)__builtin_amdgcn_readfirstlane(kpos_tile(cur)[BN - 1]) < qlo_wave;
         if (!skip) tile(cur, masked_tag);
