@@ -391,7 +391,7 @@ def calibrate_counters():
         sc.scfa_gather_rows(x, idx, out=out)
     torch.cuda.synchronize()
     assert torch.equal(out, x)
-    print(json.dumps({"calibrate_counters": "scfa::gather_rows_kernel<0>", "launches": 10,
+    print(json.dumps({"calibrate_counters": "scfa::gather_rows_kernel<0, true>", "launches": 10,
                       "bytes_read_per_launch": S * T * (2 * d + 4), "bytes_written_per_launch": S * T * 2 * d}), flush=True)
 
 

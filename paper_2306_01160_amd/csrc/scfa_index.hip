@@ -303,10 +303,10 @@ int launch_compact_keep(int n_problems, const uint8_t* keep0, const uint8_t* kee
 // ---------------------------------------------------------------------------
 // Row gather (scfa_rows.hpp).  One launch serves up to three tensors of the same shape (blockIdx.z): Q, K and V of one
 // attention call.
-template <int MODE>
+template <int MODE, bool STREAM>
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherBatch batch, int T, int chunks_per_row)
 {
-    gather_chunks<MODE, 1>(batch.p[blockIdx.z], blockIdx.y, (long long)blockIdx.x * 256 + threadIdx.x, 0, T, chunks_per_row, -1);
+    gather_chunks<MODE, 1, STREAM>(batch.p[blockIdx.z], blockIdx.y, (long long)blockIdx.x * 256 + threadIdx.x, 0, T, chunks_per_row, -1);
 }
 
 // mode as in the kernel; n_tensors 1..3 problems of identical shape
@@ -319,12 +319,12 @@ int launch_gather_rows(int n_tensors, const void* const* x, const int32_t* const
     const long long total = (long long)T * cpr;
     dim3 grid((unsigned)((total + 255) / 256), S, n_tensors);
     ProfScope prof(SCFA_K_GATHER, st);
-    if (mode == 0)
-        hipLaunchKernelGGL(gather_rows_kernel<0>, grid, dim3(256), 0, st, batch, T, cpr);
-    else if (mode == 1)
-        hipLaunchKernelGGL(gather_rows_kernel<1>, grid, dim3(256), 0, st, batch, T, cpr);
-    else
-        hipLaunchKernelGGL(gather_rows_kernel<2>, grid, dim3(256), 0, st, batch, T, cpr);
+#define SCFA_GATHER(MODE, STREAM) hipLaunchKernelGGL((gather_rows_kernel<MODE, STREAM>), grid, dim3(256), 0, st, batch, T, cpr)
+    const bool stream = gather_streams(S, T, row_bytes, false, count[0] != nullptr);
+    if (mode == 0) { if (stream) SCFA_GATHER(0, true); else SCFA_GATHER(0, false); }
+    else if (mode == 1) { if (stream) SCFA_GATHER(1, true); else SCFA_GATHER(1, false); }
+    else { if (stream) SCFA_GATHER(2, true); else SCFA_GATHER(2, false); }
+#undef SCFA_GATHER
     SCFA_HIP_TRY(hipGetLastError());
     return SCFA_OK;
 }

@@ -132,7 +132,7 @@ constexpr int GATHER_PER_THREAD = 4;   // 16-byte chunks per thread of the gathe
 // the chip idle.  The others gather, GATHER_PER_THREAD chunks in flight per thread: with one, the many short workgroups with
 // the lists' LDS attached took 60 us for 48 segments of 8192 rows (d = 64) where the gather alone took 53 and the lists 12;
 // with four the launch takes 50 us, lists included (2 x 150 MB moved: 6.0 TB/s).
-template <int MODE>
+template <int MODE, bool STREAM>
 __global__ __launch_bounds__(RANGES_THREADS) void gather_and_ranges_kernel(RangesArgs ar, GatherBatch batch, int S, int n_lists,
                                                                             int blocks_per_segment, int chunks_per_row)
 {
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(RANGES_THREADS) void gather_and_ranges_kernel(Range
     }
     const int g = blockIdx.x - n_lists;
     const int x = g % blocks_per_segment, ts = g / blocks_per_segment;
-    gather_chunks<MODE, GATHER_PER_THREAD>(batch.p[ts / S], ts % S, (long long)x * RANGES_THREADS * GATHER_PER_THREAD + threadIdx.x,
+    gather_chunks<MODE, GATHER_PER_THREAD, STREAM>(batch.p[ts / S], ts % S, (long long)x * RANGES_THREADS * GATHER_PER_THREAD + threadIdx.x,
                                            RANGES_THREADS, ar.T, chunks_per_row, (int32_t)KEY_POS_MASK);
 }
 
@@ -337,17 +337,17 @@ int launch_gather_and_ranges(int variant, const void* q, const void* k, const vo
     const long long per_seg = ((long long)T * cpr + per_wg - 1) / per_wg;
     const dim3 grid((unsigned)(n_lists + n_tensors * S * per_seg)), block(RANGES_THREADS);
     ProfScope prof(SCFA_K_GATHER, st);
-    if (mode == 1) {
-        static std::atomic<unsigned long long> lds_allowed{0};
-        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(&gather_and_ranges_kernel<1>), 144 * 1024, lds_allowed);
+    const auto launch = [&](auto kernel, std::atomic<unsigned long long>& lds_allowed) -> int {
+        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), 144 * 1024, lds_allowed);
         if (rc != SCFA_OK) return rc;
-        hipLaunchKernelGGL(gather_and_ranges_kernel<1>, grid, block, smem, st, ar, batch, S, n_lists, (int)per_seg, cpr);
-    } else {
-        static std::atomic<unsigned long long> lds_allowed{0};
-        const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(&gather_and_ranges_kernel<0>), 144 * 1024, lds_allowed);
-        if (rc != SCFA_OK) return rc;
-        hipLaunchKernelGGL(gather_and_ranges_kernel<0>, grid, block, smem, st, ar, batch, S, n_lists, (int)per_seg, cpr);
-    }
+        hipLaunchKernelGGL(kernel, grid, block, smem, st, ar, batch, S, n_lists, (int)per_seg, cpr);
+        return SCFA_OK;
+    };
+    static std::atomic<unsigned long long> lds_allowed[4];   // one for each instantiation
+    const bool stream = gather_streams(S, T, d * 2, bwd_work != nullptr, drop);
+    const int rc = mode == 1 ? (stream ? launch(&gather_and_ranges_kernel<1, true>, lds_allowed[0]) : launch(&gather_and_ranges_kernel<1, false>, lds_allowed[1]))
+                             : (stream ? launch(&gather_and_ranges_kernel<0, true>, lds_allowed[2]) : launch(&gather_and_ranges_kernel<0, false>, lds_allowed[3]));
+    if (rc != SCFA_OK) return rc;
     SCFA_HIP_TRY(hipGetLastError());
     return SCFA_OK;
 }

@@ -132,10 +132,23 @@ __device__ __forceinline__ uint4 convert_chunk(uint4 v, float scale)
     return v;
 }
 
-// chunks g0 + i * stride (i < N) of segment s: the N index reads, then the N row reads of a thread are in flight together.  The rows are
-// read past the caches: nobody reads them again (training step, 24 x 16384 rows 675 -> 672 us, 64 x 4096 x 128 457 -> 455,
-// 192 x 1024 161.4 -> 159.8, no slower anywhere).
-template <int MODE, int N>
+// Whether the rows of a gather are read past the caches.  Nobody reads them again, and where a backward follows, or K and V of a forward
+// do not fit the L2s together (32 MB), they would push out the copies that the attention reads.  Below, a caller's rows are often in
+// the caches and come faster from there.  Forward only, in us, through the caches / past them, inputs that were read a call ago (in brackets:
+// that were written just before, with those writes): rows of 8192, d = 64, 8 segments 38.6 / 40.3 (47.8 / 48.0), 12 42.3 / 46.3 (56.4 / 56.8),
+// 16 49.3 / 51.9 (67.5 / 68.0), 20 56.8 / 60.0 (83.5 / 79.5), 32 80.4 / 79.5 (120.7 / 118.9), 48 111.6 / 106.8 (171.4 / 167.4); d = 128, 4 42.8 /
+// 46.8 (51.6 / 52.0), 8 50.4 / 53.1 (67.9 / 68.2), 10 58.4 / 61.8 (84.7 / 81.8).  Training step: 8 x 8192 83.2 / 84.7 (94.6 / 94.7), 16 127.7 / 130.7
+// (152.4 / 150.8), 24 181.4 / 176.0 (210.6 / 210.1), 96 x 4096 296.8 / 287.8 (359.8 / 349.5).  QK-dropping reads
+// the rows it keeps, taken as half of them; forward, half kept: 16 x 8192 x 128 120.9 / 124.8 (163.1 / 162.5), 16 x 16384 200.2 / 203.6
+// (243.7 / 242.3), 24 x 16384 278.8 / 278.8 (337.5 / 336.8).
+inline bool gather_streams(long long S, long long T, int row_bytes, bool train, bool drop)
+{
+    return train || S * T * row_bytes > (drop ? 32LL : 16LL) << 20;
+}
+
+// chunks g0 + i * stride (i < N) of segment s: the N index reads, then the N row reads of a thread are in flight together.  (STREAM as an
+// argument and both forms of the reads in the kernel: 192 x 1024 rows 54.3 -> 57.1 us.)
+template <int MODE, int N, bool STREAM>
 __device__ __forceinline__ void gather_chunks(const GatherProblem& pr, int s, long long g0, int stride, int T, int chunks_per_row,
                                               int32_t pos_mask)
 {
@@ -153,7 +166,10 @@ __device__ __forceinline__ void gather_chunks(const GatherProblem& pr, int s, lo
     const int c = (int)(g0 % chunks_per_row);        // the stride is a whole number of rows
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        if (r[i] < n) v[i] = load_stream(x + (size_t)src[i] * chunks_per_row + c);
+        if (r[i] < n) {
+            const uint4* const from = x + (size_t)src[i] * chunks_per_row + c;
+            v[i] = STREAM ? load_stream(from) : *from;
+        }
 #pragma unroll
     for (int i = 0; i < N; ++i)
         if (r[i] < n) out[(size_t)r[i] * chunks_per_row + c] = convert_chunk<MODE>(v[i], pr.scale);
