@@ -1,9 +1,11 @@
 """Every item of every segment is done once, whatever the number of segments is to the 8 XCDs: fewer than 8, a multiple, one less
-and one more, and odd ones whose ranks are turned; one launch for both gradients and one each; tolerances as in
-test_gpu_attention_parity.py."""
+and one more, and odd ones whose ranks are turned; one launch for both gradients, and one each (which the event timers ask for), whose
+bits are the same; tolerances as in test_gpu_attention_parity.py."""
 import pytest
+import torch
 
 from gpu_util import assert_within, compare_backward, compare_forward, run_gpu
+from paper_2306_01160_amd import binding as sc
 from paper_2306_01160_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -16,3 +18,13 @@ def test_segments_and_xcds(S, T, d, nb):
     o, lse, grads, _ = run_gpu(wl)
     assert_within(compare_forward(wl, o, lse), wl.dtype)
     assert_within(compare_backward(wl, grads), wl.dtype)
+    sc.scfa_prof_reset()
+    sc.scfa_prof_enable(True)
+    try:
+        apart = run_gpu(wl)[2]
+        assert sc.scfa_prof_read("bwd_dkdv")[1] == 1 and sc.scfa_prof_read("bwd_dq")[1] == 1
+    finally:
+        sc.scfa_prof_enable(False)
+        sc.scfa_prof_reset()
+    for name, a, b in zip(("dQ", "dK", "dV"), grads, apart):
+        assert torch.equal(a, b), name
