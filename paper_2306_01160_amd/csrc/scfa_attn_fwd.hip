@@ -64,8 +64,8 @@ struct FwdRing {
 };
 
 // QK-dropping: the output rows of dropped queries are zeros and their LSE is -inf.  Every workgroup of the forward kernel, the
-// ones without work included, writes a strided share of its segment's dropped rows next to its own stores (a launch of its own
-// for them ran with nothing beside it).  key_seg: the segment's query index vector, dropped positions from n_keep on.
+// ones without work included, writes a strided share of its segment's dropped rows after its own stores (a launch of its own
+// for them ran with nothing beside it; why after: zero_dropped_rows in scfa_attn_bwd.hip).  key_seg: the segment's query index vector, dropped positions from n_keep on.
 template <int D, int THREADS>
 __device__ __forceinline__ void fill_dropped_rows(const uint32_t* __restrict__ key_seg, int n_keep, int T, int w, int n_wg,
                                                   uint16_t* __restrict__ o, float* __restrict__ lse, size_t seg)
@@ -114,10 +114,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     const int q_begin = it[W_QBEGIN], q_count = it[W_QCOUNT];
     const int k_begin = it[W_KBEGIN], k_count = it[W_KCOUNT], k_nomask = it[W_KNOMASK];
     const size_t seg = (size_t)s * T;
-    if (q_count <= 0) {   // no work: only the share of the dropped rows (n_keep_q: QK-dropping, else null)
-        if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + seg, n_keep_q[s], T, w, n_work, o, lse, seg);
-        return;
-    }
+    auto fill_dropped = [&] { if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + seg, n_keep_q[s], T, w, n_work, o, lse, seg); };
+    if (q_count <= 0) return fill_dropped();   // no work: only the share of the dropped rows (n_keep_q: QK-dropping, else null)
 
     const int tid = threadIdx.x % THREADS, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, h = lane >> 5;
 
@@ -146,7 +144,6 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
     // more of every item (192 x 1024 rows in 16 buckets 160.5 -> 158.7 us a step, 36 x 8192 272 -> 268; both gradients likewise)
 #pragma unroll
     for (int u = 0; u < NBUF - 1; ++u) issue(u * KS + group, u);
-    if (n_keep_q) fill_dropped_rows<D, THREADS * KS>(q_key + seg, n_keep_q[s], T, w, n_work, o, lse, seg);
 
     int cur = 0;
     auto refill_of = [&] { return cur == 0 ? NBUF - 1 : cur - 1; };    // the buffer of the tile before
@@ -164,7 +161,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
         }
         wait_async<0>();
         for (int i = 0; i < KS; ++i) lds_barrier();
-        return;
+        return fill_dropped();
     }
 
     int qrow[QB], qpos[QB];
@@ -444,7 +441,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
             ml[64 + lane] = lsum[0];
         }
         lds_barrier();
-        if (group == 1) return;
+        if (group == 1) return fill_dropped();
         const float m_other = ml[lane], m_new = fmaxf(m[0], m_other), m_use = m_new == -INFINITY ? 0.f : m_new;
         const float mine = fast_exp2((m[0] - m_use) * cexp), theirs = fast_exp2((m_other - m_use) * cexp);   // -inf: 0
         lsum[0] = fmaf(lsum[0], mine, ml[64 + lane] * theirs);
@@ -498,6 +495,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
             stage.template store<false>(q_out, n_rows, lane, [&](int row) { return seg + (size_t)(q_begin + (wave * QB + b) * 32 + row); });
         }
     }
+    fill_dropped();
 }
 
 // Whether two groups of wavefronts share the key tiles of an item.  A launch that cannot give every CU two or three workgroups is
