@@ -132,18 +132,19 @@ __device__ __forceinline__ uint4 convert_chunk(uint4 v, float scale)
     return v;
 }
 
-// Whether the rows of a gather are read past the caches.  Nobody reads them again, and where a backward follows, or K and V of a forward
-// do not fit the L2s together (32 MB), they would push out the copies that the attention reads.  Below, a caller's rows are often in
-// the caches and come faster from there.  Forward only, in us, through the caches / past them, inputs that were read a call ago (in brackets:
-// that were written just before, with those writes): rows of 8192, d = 64, 8 segments 38.6 / 40.3 (47.8 / 48.0), 12 42.3 / 46.3 (56.4 / 56.8),
-// 16 49.3 / 51.9 (67.5 / 68.0), 20 56.8 / 60.0 (83.5 / 79.5), 32 80.4 / 79.5 (120.7 / 118.9), 48 111.6 / 106.8 (171.4 / 167.4); d = 128, 4 42.8 /
-// 46.8 (51.6 / 52.0), 8 50.4 / 53.1 (67.9 / 68.2), 10 58.4 / 61.8 (84.7 / 81.8).  Training step: 8 x 8192 83.2 / 84.7 (94.6 / 94.7), 16 127.7 / 130.7
-// (152.4 / 150.8), 24 181.4 / 176.0 (210.6 / 210.1), 96 x 4096 296.8 / 287.8 (359.8 / 349.5).  QK-dropping reads
-// the rows it keeps, taken as half of them; forward, half kept: 16 x 8192 x 128 120.9 / 124.8 (163.1 / 162.5), 16 x 16384 200.2 / 203.6
-// (243.7 / 242.3), 24 x 16384 278.8 / 278.8 (337.5 / 336.8).
+// Whether the rows of a gather are read past the caches.  Nobody reads them again, and where K and V do not fit the L2s together (32 MB;
+// with a backward, where Q is copied as well, 22 MB) they would push out the copies that the attention reads.  Below, a caller's rows are
+// often in the caches and come faster from there.  In us, through the caches / past them, inputs that were read a call ago (in brackets: that were
+// written just before, with those writes); segments of 8192 rows where nothing else is said.
+// Forward only, d = 64, 8 segments 38.6 / 40.3 (47.8 / 48.0), 12 42.3 / 46.3 (56.4 / 56.8), 16 49.3 / 51.9 (67.5 / 68.0), 20 56.8 / 60.0 (83.5 / 79.5),
+// 32 80.4 / 79.5 (120.7 / 118.9), 48 111.6 / 106.8 (171.4 / 167.4); d = 128, 4 42.8 / 46.8 (51.6 / 52.0), 8 50.4 / 53.1 (67.9 / 68.2), 10 58.4 / 61.8
+// (84.7 / 81.8).  Training step, 12 x 4164 65.7 / 68.9 (74.9 / 74.8), 8 83.2 / 84.7 (94.6 / 94.7), 10 95.4 / 97.3 (108.1 / 109.4), 12 105.2 / 108.1 (123.0 /
+// 121.2), 16 127.7 / 130.7 (152.4 / 150.8), 24 181.4 / 176.0 (210.6 / 210.1), 96 x 4096 296.8 / 287.8 (359.8 / 349.5).
+// QK-dropping reads the rows it keeps, taken as half of them.  Half kept, forward, 16 x 8192 x 128 120.9 / 124.8 (163.1 / 162.5), 16 x 16384 200.2 / 203.6
+// (243.7 / 242.3), 24 x 16384 278.8 / 278.8 (337.5 / 336.8); training step, 16 224.0 / 227.7 (247.2 / 246.0), 20 262.2 / 265.8 (290.8 / 290.7).
 inline bool gather_streams(long long S, long long T, int row_bytes, bool train, bool drop)
 {
-    return train || S * T * row_bytes > (drop ? 32LL : 16LL) << 20;
+    return S * T * row_bytes > (train ? 11LL : 16LL) * (drop ? 2 : 1) << 20;
 }
 
 // chunks g0 + i * stride (i < N) of segment s: the N index reads, then the N row reads of a thread are in flight together.  (STREAM as an

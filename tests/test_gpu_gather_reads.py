@@ -11,8 +11,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,d", [(4999, 64), (4099, 128)])
 @pytest.mark.parametrize("drop", [False, True])
-def test_forward_on_both_sides_of_the_limit(T, d, drop):
-    S = ((32 if drop else 16) << 20) // (T * d * 2) + 1
+@pytest.mark.parametrize("train", [False, True])
+def test_forward_on_both_sides_of_the_limit(T, d, drop, train):
+    S = ((11 if train else 16) * (2 if drop else 1) << 20) // (T * d * 2) + 1
     gen = torch.Generator(device="cuda"); gen.manual_seed(T)
     q, k, v = (torch.randn((1, S, T, d), device="cuda", generator=gen).bfloat16() for _ in range(3))
     lq, lk = (torch.randint(0, 2 if drop else 9, (1, S, T), device="cuda", generator=gen, dtype=torch.int32) for _ in range(2))
@@ -20,7 +21,7 @@ def test_forward_on_both_sides_of_the_limit(T, d, drop):
         lq, lk = lq.to(torch.uint8), lk.to(torch.uint8)
     def forward(i0, i1):
         part = [x[:, i0:i1] for x in (q, k, v, lq, lk)]
-        return (pipeline.qkdrop_forward(*part, 0.125, need_bwd=False) if drop else pipeline.hash_forward(*part, 9, 0.125, need_bwd=False))[:2]
+        return (pipeline.qkdrop_forward(*part, 0.125, need_bwd=train) if drop else pipeline.hash_forward(*part, 9, 0.125, need_bwd=train))[:2]
     whole = forward(0, S)
     for i0, i1 in ((0, S - 1), (1, S)):
         for name, x, part in zip(("O", "LSE"), whole, forward(i0, i1)):
