@@ -151,7 +151,10 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
         const int key = jt * BN + wave * KPW + lane;
         if (lane < KPW && key >= k_count) kpos_tile(cur)[wave * KPW + lane] = KEY_PAST_END;
     };
-    if (wave * (QB * 32) >= q_count) {   // a wavefront without rows only loads (scfa_attn_bwd.hip, dkdv_item)
+    // a wavefront without rows only loads (scfa_attn_bwd.hip, dkdv_item); at d = 128 its steps leave out the products, and the compiler orders the
+    // tiles of the others better beside that test (forward of 1 x 65536 rows, half kept, with a loop of its own / so 473 / 456 us, 2 x 37504 385 / 378)
+    const bool idle = wave * (QB * 32) >= q_count;
+    if (D == 64 && idle) {
         for (int jt = 0; jt < n_tiles; jt += KS) {
             wait_async<LOADS_PER_TILE * (NBUF - 2)>();
             mark_end(jt + group);
@@ -414,8 +417,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
         issue(jt + (NBUF - 1) * KS, refill_of());
         // sort keys ascend along the keys of an item: a tile that lies entirely above or entirely
         // below what the queries of this wavefront may attend to contributes nothing to it
-        bool skip = false;
-        if (MASKED)
+        bool skip = D == 128 && idle;
+        if (MASKED && !skip)
             skip = (uint32_t)__builtin_amdgcn_readfirstlane(kpos_tile(cur)[0]) > qhi_wave ||
                    (uint32_t)__builtin_amdgcn_readfirstlane(kpos_tile(cur)[BN - 1]) < qlo_wave;
         if (!skip) tile(cur, masked_tag);
