@@ -328,14 +328,16 @@ def measure(name, steps, warmup, dense_twin=True):
         "value": pairs * 14 * d / (ms * 1e-3) / 1e12, "ms_per_step": ms,
         "roofline": {"bound": "mfma", "kernel": dominant, "achieved": ach, "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS,
-                     "traffic": measured_traffic(dominant, name), "avg_launch_ms": kt[dominant]["avg_ms"]},
+                     "traffic": measured_traffic(dominant, name), "avg_launch_ms": kt[dominant]["avg_ms"],
+                     "launch": "of its own, under the event timers" + ("" if drop or dominant == "fwd" else
+                               "; in the timed step one launch takes its items and those of the other gradient")},
         "computed_tile_tflops_kernels": tile_flops / (attn_ms * 1e-3) / 1e12,
         "computed_tile_frac_of_mfma_peak": tile_flops / (attn_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
         "dense_equiv_tflops": 7.0 * T * T * d * S / (ms * 1e-3) / 1e12,
         "allowed_pairs": pairs, "fwd_tiles": fwd_tiles, "bwd_tiles": bwd_tiles,
         "attn_kernels_ms_per_step": attn_ms, "kernels": kt,
-        "kernels_note": "under the event timers, which give each gradient kernel a launch; where the two share one in the "
-                        "timed step (buckets of up to 1024 tokens on average, or few items) the step is shorter than their sum", "hbm": hbm_passes(wl, kt, job.ctx),
+        "kernels_note": "under the event timers, which give each gradient kernel a launch; " +
+                        ("so does the timed step" if drop else "the timed step takes both in one, attn_bwd_f16_kernel"), "hbm": hbm_passes(wl, kt, job.ctx),
     }
     extra = {"wl": wl, "job": job}
     if dense_twin:

@@ -67,11 +67,17 @@ constexpr uint32_t KEY_PAST_END = 0xffffffffu;   // rows past the end of a ragge
 constexpr uint32_t KEY_NEVER = 0xfffffffeu;      // lower end of the range of a row that may match nothing
 
 // ---- streams ----------------------------------------------------------------------
-// Sixteen bytes that no kernel of the path reads again.  As ordinary stores the results of a training step (O, the fp32 gradients,
+// Sixteen bytes that no kernel of a forward or a training step reads again (a backward that is given no fp16 copy of O reads O).  As ordinary
+// stores the results of a training step (O, the fp32 gradients,
 // zeros of dropped rows: 350 MB at 48 x 8192 x 64 rows) take the place of the permuted copies in L2 and the 256 MB behind it, which
 // the kernels still read: 373 -> 355 us a step there, 36 x 5003 rows 184 -> 176, 192 x 1024 169 -> 161, 24 x 16384 698 -> 678.  Only for
 // instructions that write whole cache lines: smaller pieces are then not put together any more (dK/dV with 32-byte pieces 40 % slower
 // at 24 x 16384 rows, 2.5 times at 48 x 8192).
+// Whoever reads the results next finds less of them in the caches.  With O transposed and the gradients rounded to bf16 right behind the
+// step, ordinary / streaming stores, without these readers in brackets: 32 x 1024 rows 71.6 / 72.0 (47.8 / 45.7), 32 x 2048 92.4 / 92.6 (67.8 / 65.7),
+// 16 x 8192 177.9 / 177.8 (135.2 / 129.8), 192 x 1024 232.3 / 228.7 (168.4 / 160.2), 32 x 8192 329.9 / 318.8 (246.8 / 231.8), 48 x 8192 471.8 /
+// 465.2 (356.5 / 338.7), 32 x 4096 x 128 341.1 / 324.1 (253.7 / 240.3), QK-dropping 16 x 4096 x 128 161.4 / 163.6 (118.4 / 114.2): up to about
+// 130000 rows of 64 the reader loses what the step gains, above both gain.
 typedef unsigned int u32v4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_stream(uint4* p, uint4 x) { __builtin_nontemporal_store(__builtin_bit_cast(u32v4, x), reinterpret_cast<u32v4*>(p)); }
 __device__ __forceinline__ uint4 load_stream(const uint4* p) { return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32v4*>(p))); }
