@@ -141,7 +141,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
                         (wave * KPW + lane) * 4, jt * BN * 4);
     };
     // the first tiles are on their way while the rows of the item are fetched and looked at: behind them they were one memory latency
-    // more of every item (192 x 1024 rows in 16 buckets 160.5 -> 158.7 us a step, 36 x 8192 272 -> 268; both gradients likewise)
+    // more of every item (192 x 1024 rows in 16 buckets 160.5 -> 158.7 us a step, 36 x 8192 272 -> 268; both gradients likewise, but for dK/dV at d = 128)
 #pragma unroll
     for (int u = 0; u < NBUF - 1; ++u) issue(u * KS + group, u);
 
