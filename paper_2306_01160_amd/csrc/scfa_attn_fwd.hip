@@ -151,8 +151,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(D 
         const int key = jt * BN + wave * KPW + lane;
         if (lane < KPW && key >= k_count) kpos_tile(cur)[wave * KPW + lane] = KEY_PAST_END;
     };
-    // a wavefront without rows only loads (scfa_attn_bwd.hip, dkdv_item); at d = 128 its steps leave out the products, and the compiler orders the
-    // tiles of the others better beside that test (forward of 1 x 65536 rows, half kept, with a loop of its own / so 473 / 456 us, 2 x 37504 385 / 378)
+    // A wavefront without rows only loads (see dkdv_item).  In a loop of its own at d = 64, where the steps of the others are ordered worse with a
+    // test (forward of 24 x 16384 rows in one bucket, loop / test 910 / 921 us, QK-dropping 16 x 16384 half kept 189 / 200); by a test in every
+    // step at d = 128, where they are ordered better with it (1 x 65536 half kept 473 / 456, 2 x 37504 385 / 378).
     const bool idle = wave * (QB * 32) >= q_count;
     if (D == 64 && idle) {
         for (int jt = 0; jt < n_tiles; jt += KS) {
